@@ -1,6 +1,7 @@
 // endgame.hip -- the endgame DAG solver (Section VIII) for batches of
 // roots, its binning by empty cells, and the resident-section lookup.
 #include "device_common.h"
+#include "pairs.h"
 
 namespace pg {
 
@@ -294,27 +295,23 @@ __global__ void __launch_bounds__(256)
     }
 }
 
-// Bucket starts, most empty cells first.
-__global__ void eval_scan_kernel(const int *count, int *start, int *cursor)
+// First position of each bin, most empty cells first ([11]: invalid boards,
+// after all others).
+__device__ __forceinline__ int bin_start(const int *count, int e)
 {
-    if (threadIdx.x != 0) return;
     int acc = 0;
-    for (int e = 10; e >= 0; e--) {
-        start[e] = acc;
-        cursor[e] = 0;
-        acc += count[e];
-    }
-    start[11] = acc;
-    cursor[11] = 0;
+    for (int k = 10; k > (e == 11 ? -1 : e); k--) acc += count[k];
+    return acc;
 }
 
 // Roots into their bins: positions inside the workgroup from LDS counters,
 // one global reservation per bin per workgroup.
 __global__ void __launch_bounds__(256)
-    eval_scatter_kernel(const uint8_t *empties, size_t n, const int *start, int *cursor, int *order)
+    eval_scatter_kernel(const uint8_t *empties, size_t n, const int *count, int *start, int *cursor, int *order)
 {
     __shared__ int lc[11], base[11];
     if (threadIdx.x < 11) lc[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 12) start[threadIdx.x] = bin_start(count, (int)threadIdx.x);
     __syncthreads();
     int ee[kBinPer], local[kBinPer];
 #pragma unroll
@@ -324,131 +321,209 @@ __global__ void __launch_bounds__(256)
         local[r] = ee[r] <= 10 ? atomicAdd(&lc[ee[r]], 1) : 0;
     }
     __syncthreads();
-    if (threadIdx.x < 11 && lc[threadIdx.x]) base[threadIdx.x] = atomicAdd(&cursor[threadIdx.x], lc[threadIdx.x]);
+    if (threadIdx.x < 11 && lc[threadIdx.x])
+        base[threadIdx.x] = bin_start(count, (int)threadIdx.x) + atomicAdd(&cursor[threadIdx.x], lc[threadIdx.x]);
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kBinPer; r++) {
         const size_t i = ((size_t)blockIdx.x * kBinPer + r) * 256 + threadIdx.x;
-        if (ee[r] <= 10) order[start[ee[r]] + base[ee[r]] + local[r]] = (int)i;
+        if (ee[r] <= 10) order[base[ee[r]] + local[r]] = (int)i;
     }
 }
 
-__global__ void zero_ints_kernel(int *p, int n)
+// Counts, cursors and queue counters cleared (a kernel, not a memset, so the
+// sequence can be captured in a graph).
+__global__ void eval_clear_kernel(int *count, int *cursor, unsigned long long *counter)
 {
-    for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
+    if (threadIdx.x < 16) count[threadIdx.x] = cursor[threadIdx.x] = 0;
+    if (threadIdx.x < 4) counter[threadIdx.x] = 0;
+}
+
+// The whole binning of a small batch by one workgroup: for a few thousand
+// boards the three launches of the general form cost more than their work
+// (launches of a few microseconds each; 4096 boards: 21 us against 8).
+constexpr int kBinSmall = 8192;
+__global__ void __launch_bounds__(1024)
+    eval_bin_small_kernel(const uint64_t *boards, int n, int *start, int *order, unsigned long long *counter,
+                          int *status, uint4 *out)
+{
+    __shared__ int lc[12], base[12];
+    if (threadIdx.x < 12) lc[threadIdx.x] = 0;
+    if (threadIdx.x < 4) counter[threadIdx.x] = 0;
+    __syncthreads();
+    int e[kBinSmall / 1024], local[kBinSmall / 1024];
+#pragma unroll
+    for (int r = 0; r < kBinSmall / 1024; r++) {
+        const int i = r * 1024 + (int)threadIdx.x;
+        e[r] = -1;
+        if (i < n) {
+            const RootInfo R = decode_root(boards[i]);
+            e[r] = R.valid ? R.e : 11;
+            local[r] = atomicAdd(&lc[e[r]], 1);
+            if (!R.valid) {
+                const uint4 z = make_uint4(0, 0, 0, 0);
+                out[4 * i] = z; out[4 * i + 1] = z; out[4 * i + 2] = z; out[4 * i + 3] = z;
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 12) {
+        base[threadIdx.x] = start[threadIdx.x] = bin_start(lc, (int)threadIdx.x);
+        if (threadIdx.x == 11 && status && lc[11]) atomicAdd(status, lc[11]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kBinSmall / 1024; r++)
+        if (e[r] >= 0 && e[r] <= 10) order[base[e[r]] + local[r]] = r * 1024 + (int)threadIdx.x;
 }
 
 // Persistent solve over all valid roots, most empty cells first.  The roots
-// are binned by number of empty cells on the device; three persistent
-// launches follow one another on the stream, one per LDS class, each taking
-// roots from its own device work queue (no host synchronisation):
-//   class 0: 8 to 10 empty cells, a workgroup per root (9 and 10 keep their
-//            layers in the workgroup's slot of a global buffer; only the
-//            first `slots` workgroups own a slot: they take the 9-10 queue
-//            first, then join the others on the 8-empty queue);
-//   class 1: 7 empty cells, a workgroup per root, a smaller LDS footprint;
-//   class 2: up to kWaveMaxEmpties, synchronised per wave only: a wave
-//            solves eight roots with up to 3 empty cells at once (8 lanes
-//            each), four with 4 (16 lanes), two with 5 (32 lanes) or one
-//            with 6, each on its own part of the wave's LDS.
-constexpr int kWaveMaxEmpties = 6;
-// two layers of the widest 6-empty layer, then the five-set tables (C(6,3) = 20)
-constexpr int kWaveLdsBytes = 2 * 90 * 64 + 2 * 20 * 32;
+// are binned by number of empty cells on the device; persistent launches
+// follow one another on the stream, one per LDS class, each taking roots from
+// its own device work queue (no host synchronisation).  The first item of a
+// workgroup is its own number, the queue counter gives the items after
+// those: a launch that finds nothing to do ends without an atomic (the
+// workgroups' atomics on one counter took 39 us in a launch of 3072 waves).
+//   deepest: 9 and 10 empty cells, a workgroup per root, its layers in the
+//            workgroup's slot of a global buffer;
+//   class 0: 8 empty cells, a workgroup per pair of roots (155 KB of LDS);
+//   class 1: 7 empty cells, a workgroup per pair (69 KB);
+//   class 2: up to 6: a workgroup of 256 threads takes one pair of roots with
+//            6 empty cells, two pairs with 5, four with 4 or eight with fewer
+//            (30 to 33 KB).
+constexpr int kClass2Threads = 256;
+constexpr int kClass2LdsBytes = PairDag<6>::lds_bytes;
+static_assert(2 * PairDag<5>::lds_bytes <= kClass2LdsBytes && 4 * PairDag<4>::lds_bytes <= kClass2LdsBytes &&
+              8 * PairDag<3>::lds_bytes <= kClass2LdsBytes, "class 2 LDS");
 
-template <int CLS, int NT>
+__host__ __device__ constexpr int class2_pairs(int e) { return e == 6 ? 1 : e == 5 ? 2 : e == 4 ? 4 : 8; }
+
+template <int NT>
 __global__ void __launch_bounds__(NT)
-    eval_persistent_kernel(const uint64_t *boards, const int *order, const int *start,
-                           unsigned long long *counter, uint4 *out, uint4 *gl, int slots, DevTables T)
+    eval_deepest_kernel(const uint64_t *boards, const int *order, const int *start, unsigned long long *counter,
+                        uint4 *out, uint4 *gl, DevTables T)
 {
     extern __shared__ uint4 lds[];
-    __shared__ long long s_item;
-    __shared__ int s_slots[4][2][10];
-    // bins are ordered by empty cells, most first: e occupies [start[e], start[e - 1])
-    const int lo = CLS == 0 ? 0 : CLS == 1 ? start[7] : start[kWaveMaxEmpties];
-    const int hi = CLS == 0 ? start[7] : CLS == 1 ? start[kWaveMaxEmpties] : start[11];
-    if constexpr (CLS < 2) {
-        // class 0: roots with 9 or 10 empty cells, [0, big), come from queue 3
-        // and only go to workgroups that own a global layer slot; the rest of
-        // the class, [big, hi), from queue 0.  Class 1 uses queue 1 only.
-        const int big = CLS == 0 ? start[8] : lo;
-        if (CLS == 0 && (int)blockIdx.x < slots) {
-            uint4 *mine = gl + (size_t)blockIdx.x * 2 * 4 * kDagGlobalLayer;
-            for (;;) {
-                if (threadIdx.x == 0) s_item = (long long)atomicAdd(&counter[3], 1ull);
-                __syncthreads();
-                const long long item = s_item;
-                __syncthreads();
-                if (item >= big) break;
-                const int root = order[item];
-                const RootInfo R = decode_root(boards[root]);
-                solve_root<NT>(R, T, mine, mine + 4 * kDagGlobalLayer, kDagGlobalLayer, lds, out + 4 * (size_t)root,
-                                s_slots[0][0], s_slots[0][1]);
-                __syncthreads();
-            }
-        }
-        for (;;) {
-            if (threadIdx.x == 0) s_item = (long long)atomicAdd(&counter[CLS], 1ull);
-            __syncthreads();
-            const long long item = big + s_item;
-            __syncthreads();
-            if (item >= hi) break;
-            const int root = order[item];
-            const RootInfo R = decode_root(boards[root]);
-            solve_root<NT>(R, T, lds, lds + 4 * T.dag_max[R.e], T.dag_max[R.e], lds + 8 * T.dag_max[R.e],
-                            out + 4 * (size_t)root, s_slots[0][0], s_slots[0][1]);
-            __syncthreads();
-        }
-    } else {
-        // A wave takes a chunk of K roots of one bin (K = 8 up to 3 empty
-        // cells, 4 for 4, 2 for 5, 1 for 6: the widest layers have 6, 12, 30
-        // and 90 nodes); the roots of a chunk have the same layers, so the wave
-        // synchronises them together.  Chunks are numbered bin by bin, most
-        // empty cells first; the last chunk of a bin repeats the bin's last
-        // root where it runs short (the copy writes the same bytes).
-        __shared__ int s_sub[4][8][2][kWaveMaxEmpties];
-        (void)lo;
-        (void)hi;
-        const int w = threadIdx.x >> 6, wl = threadIdx.x & 63;
-        uint4 *wb = lds + (size_t)w * (kWaveLdsBytes / 16);
-        for (;;) {
-            unsigned long long got = 0;
-            if (wl == 0) got = atomicAdd(&counter[2], 1ull);
-            const long long c = (long long)__shfl(got, 0, 64);
-            int e = -1, K = 1, base = 0, last = 0;
-            long long cum = 0;
-            for (int b = kWaveMaxEmpties; b >= 0; b--) {
-                const int blo = start[b], bhi = b == 0 ? start[11] : start[b - 1];
-                const int kb = b <= 3 ? 8 : b == 4 ? 4 : b == 5 ? 2 : 1;
-                const long long nch = (bhi - blo + kb - 1) / kb;
-                if (e < 0 && c < cum + nch) {
-                    e = b;
-                    K = kb;
-                    base = blo + (int)(c - cum) * kb;
-                    last = bhi - 1;
-                }
-                cum += nch;
-            }
-            if (e < 0) break;
-            const int g = wl / (64 / K);
-            const int root = order[min(base + g, last)];
-            const RootInfo R = decode_root(boards[root]);
-            uint4 *o = out + 4 * (size_t)root;
-            if (K == 8) {
-                uint4 *sb = wb + g * 100;   // 1.6 KB each: layers of 6 nodes, tables of 3 subsets
-                solve_root<8>(R, T, sb, sb + 4 * 6, 6, sb + 8 * 6, o, s_sub[w][g][0], s_sub[w][g][1]);
-            } else if (K == 4) {
-                uint4 *sb = wb + g * 200;   // 3.2 KB each: layers of 12 nodes, tables of 6 subsets
-                solve_root<16>(R, T, sb, sb + 4 * 12, 12, sb + 8 * 12, o, s_sub[w][g][0], s_sub[w][g][1]);
-            } else if (K == 2) {
-                uint4 *sb = wb + g * 400;   // 6.4 KB each: layers of 30 nodes, tables of 10 subsets
-                solve_root<32>(R, T, sb, sb + 4 * 30, 30, sb + 8 * 30, o, s_sub[w][g][0], s_sub[w][g][1]);
-            } else {
-                solve_root<64>(R, T, wb, wb + 4 * 90, 90, wb + 8 * 90, o, s_sub[w][0][0], s_sub[w][0][1]);
-            }
-            wave_sync();
-        }
+    __shared__ int s_item;
+    __shared__ int s_slots[2][10];
+    const int n = start[8];
+    uint4 *mine = gl + (size_t)blockIdx.x * 2 * 4 * kDagGlobalLayer;
+    for (int item = blockIdx.x; item < n;) {
+        const int root = order[item];
+        const RootInfo R = decode_root(boards[root]);
+        solve_root<NT>(R, T, mine, mine + 4 * kDagGlobalLayer, kDagGlobalLayer, lds, out + 4 * (size_t)root,
+                       s_slots[0], s_slots[1]);
+        __syncthreads();
+        if (threadIdx.x == 0) s_item = (int)(gridDim.x + atomicAdd(&counter[3], 1ull));
+        __syncthreads();
+        item = s_item;
     }
 }
+
+template <int E, int NT, int PAIRS>
+__device__ __forceinline__ void solve_bin_chunk(const uint64_t *boards, const int *order, int first, int last,
+                                                uint4 *out, uint4 *lds, const DevTables &T)
+{
+    // this thread's pair; beyond the end of the bin the last root is repeated
+    // (the copies write the same bytes)
+    const int i = first + 2 * ((int)threadIdx.x / (NT / PAIRS));
+    const int r0 = order[min(i, last)], r1 = order[min(i + 1, last)];
+    const uint64_t b[2] = {boards[r0], boards[r1]};
+    uint4 *const o[2] = {out + 4 * (size_t)r0, out + 4 * (size_t)r1};
+    solve_pairs<E, NT, PAIRS>(b, o, T, lds);
+}
+
+template <int CLS, int NT>
+__global__ void __launch_bounds__(NT, CLS == 0 && NT == 512 ? 2 : 4)
+    eval_pairs_kernel(const uint64_t *boards, const int *order, const int *start, unsigned long long *counter,
+                      uint4 *out, DevTables T)
+{
+    extern __shared__ uint4 lds[];
+    __shared__ int s_item;
+    for (int item = blockIdx.x;;) {
+        // bins are ordered by empty cells, most first: e occupies
+        // [start[e], start[e - 1]), 0 ends at start[11]
+        if constexpr (CLS < 2) {
+            constexpr int E = 8 - CLS;
+            const int first = start[E] + 2 * item, end = start[E - 1];
+            if (first >= end) break;
+            solve_bin_chunk<E, NT, 1>(boards, order, first, end - 1, out, lds, T);
+        } else {
+            int e = -1, first = 0, last = 0, cum = 0;
+            for (int b = 6; b >= 0; b--) {
+                const int lo = start[b], hi = b == 0 ? start[11] : start[b - 1], per = 2 * class2_pairs(b);
+                const int chunks = (hi - lo + per - 1) / per;
+                if (e < 0 && item < cum + chunks) {
+                    e = b;
+                    first = lo + (item - cum) * per;
+                    last = hi - 1;
+                }
+                cum += chunks;
+            }
+            if (e < 0) break;
+            switch (e) {
+            case 6: solve_bin_chunk<6, NT, class2_pairs(6)>(boards, order, first, last, out, lds, T); break;
+            case 5: solve_bin_chunk<5, NT, class2_pairs(5)>(boards, order, first, last, out, lds, T); break;
+            case 4: solve_bin_chunk<4, NT, class2_pairs(4)>(boards, order, first, last, out, lds, T); break;
+            case 3: solve_bin_chunk<3, NT, class2_pairs(3)>(boards, order, first, last, out, lds, T); break;
+            case 2: solve_bin_chunk<2, NT, class2_pairs(2)>(boards, order, first, last, out, lds, T); break;
+            case 1: solve_bin_chunk<1, NT, class2_pairs(1)>(boards, order, first, last, out, lds, T); break;
+            default: solve_bin_chunk<0, NT, class2_pairs(0)>(boards, order, first, last, out, lds, T); break;
+            }
+        }
+        if (threadIdx.x == 0) s_item = (int)(gridDim.x + atomicAdd(&counter[CLS], 1ull));
+        __syncthreads();
+        item = s_item;
+        __syncthreads();
+    }
+}
+
+// A few boards in one launch, a workgroup per board and no binning (as many
+// boards as run at once): a board with up to 8 empty cells is solved as a
+// pair of itself.  One board is launch latency and the layers' chain: 113 us
+// through the binned launches, all of them waiting for one another.
+template <int E>
+__device__ __forceinline__ void solve_one(uint64_t board, uint4 *out, const DevTables &T, uint4 *lds)
+{
+    const uint64_t b[2] = {board, board};
+    uint4 *const o[2] = {out, out};
+    solve_pairs<E, 1024, 1>(b, o, T, lds);
+}
+
+__global__ void __launch_bounds__(1024)
+    eval_few_kernel(const uint64_t *boards, int *status, uint4 *out, uint4 *gl, DevTables T)
+{
+    extern __shared__ uint4 lds[];
+    __shared__ int s_slots[2][10];
+    uint4 *o = out + 4 * (size_t)blockIdx.x;
+    const uint64_t b = boards[blockIdx.x];
+    const RootInfo R = decode_root(b);
+    switch (R.valid ? R.e : 11) {
+    case 0: solve_one<0>(b, o, T, lds); break;
+    case 1: solve_one<1>(b, o, T, lds); break;
+    case 2: solve_one<2>(b, o, T, lds); break;
+    case 3: solve_one<3>(b, o, T, lds); break;
+    case 4: solve_one<4>(b, o, T, lds); break;
+    case 5: solve_one<5>(b, o, T, lds); break;
+    case 6: solve_one<6>(b, o, T, lds); break;
+    case 7: solve_one<7>(b, o, T, lds); break;
+    case 8: solve_one<8>(b, o, T, lds); break;
+    case 9:
+    case 10: {
+        uint4 *mine = gl + (size_t)blockIdx.x * 2 * 4 * kDagGlobalLayer;
+        solve_root<1024>(R, T, mine, mine + 4 * kDagGlobalLayer, kDagGlobalLayer, lds, o, s_slots[0], s_slots[1]);
+        break;
+    }
+    default:
+        if (threadIdx.x < 4) o[threadIdx.x] = make_uint4(0, 0, 0, 0);
+        if (threadIdx.x == 0 && status) atomicAdd(status, 1);
+    }
+}
+
+// Roots with up to kWaveMaxEmpties empty cells solved by one wave each: two
+// layers of the widest 6-empty layer, then the five-set tables (C(6,3) = 20).
+constexpr int kWaveMaxEmpties = 6;
+constexpr int kWaveLdsBytes = 2 * 90 * 64 + 2 * 20 * 32;
 
 // A batch whose roots all fall in one class (the server batches its searches
 // by empty cells): the roots are taken in order from one device queue, with
@@ -581,22 +656,20 @@ hipError_t launch_eval_bin(const uint64_t *boards, size_t n, const EvalScratch &
                            uint4 *out, const DevTables &T, hipStream_t s)
 {
     (void)T;
-    hipLaunchKernelGGL(zero_ints_kernel, dim3(1), dim3(64), 0, s, S.count, 16);
-    if (n) {
-        const unsigned g = (unsigned)((n + 256 * kBinPer - 1) / (256 * kBinPer));
-        hipLaunchKernelGGL(eval_count_kernel, dim3(g), dim3(256), 0, s, boards, n, S.count,
-                           S.empties, status, out);
+    if (n <= (size_t)kBinSmall) {
+        hipLaunchKernelGGL(eval_bin_small_kernel, dim3(1), dim3(1024), 0, s, boards, (int)n, S.start, S.order,
+                           S.counter, status, out);
+        return hipGetLastError();
     }
-    hipLaunchKernelGGL(eval_scan_kernel, dim3(1), dim3(64), 0, s, S.count, S.start, S.cursor);
-    if (n) {
-        const unsigned g = (unsigned)((n + 256 * kBinPer - 1) / (256 * kBinPer));
-        hipLaunchKernelGGL(eval_scatter_kernel, dim3(g), dim3(256), 0, s, S.empties, n, S.start,
-                           S.cursor, S.order);
-    }
+    hipLaunchKernelGGL(eval_clear_kernel, dim3(1), dim3(64), 0, s, S.count, S.cursor, S.counter);
+    const unsigned g = (unsigned)((n + 256 * kBinPer - 1) / (256 * kBinPer));
+    hipLaunchKernelGGL(eval_count_kernel, dim3(g), dim3(256), 0, s, boards, n, S.count, S.empties, status, out);
+    hipLaunchKernelGGL(eval_scatter_kernel, dim3(g), dim3(256), 0, s, S.empties, n, S.count, S.start, S.cursor,
+                       S.order);
     return hipGetLastError();
 }
 
-// Dynamic LDS of each persistent class.
+// Dynamic LDS of each class of the server's batches (launch_eval_direct).
 static int eval_class_lds_bytes(int cls)
 {
     if (cls == 0) return std::max(dag_lds_bytes(8), std::max(dag_ftab_bytes(9), dag_ftab_bytes(10)));
@@ -611,15 +684,8 @@ static hipError_t allow_lds(const void *kernel, int bytes)
     return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
-hipError_t launch_eval_persistent(const uint64_t *boards, size_t n, uint4 *out,
-                                  const EvalScratch &S, int grid, const DevTables &T,
-                                  hipStream_t s)
-{
-    return launch_eval_persistent_slots(boards, n, out, S, grid, grid, T, s);
-}
-
-// Workgroup size of the persistent classes 0 and 1 (256 or 512 threads per
-// root; class 2 solves roots by waves in 256-thread workgroups).
+// Threads per root of 8 to 10 and of 7 empty cells (256 or 512): a pair of
+// roots with 8 or 7 takes twice as many.
 static int g_class_threads[2] = {512, 256};
 
 void set_eval_class_threads(int c0, int c1)
@@ -634,51 +700,76 @@ void get_eval_class_threads(int *c0, int *c1)
     *c1 = g_class_threads[1];
 }
 
-template <int CLS, int NT>
-static hipError_t launch_class(int g, int lds, hipStream_t s, const uint64_t *boards, const EvalScratch &S,
-                               uint4 *out, int slots, const DevTables &T)
+// Persistent grid: the kernel's occupancy times the CU count, or a workgroup
+// per item if there are fewer.
+static hipError_t persistent_grid(const void *kernel, int threads, int lds, size_t items, unsigned *grid)
 {
-    const hipError_t e = allow_lds((const void *)eval_persistent_kernel<CLS, NT>, lds);
+    int dev = 0, cus = 0, per = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess) e = allow_lds(kernel, lds);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, lds);
+    *grid = (unsigned)std::min<size_t>(items, (size_t)std::max(1, per) * (size_t)std::max(1, cus));
+    return e;
+}
+
+template <int CLS, int NT>
+static hipError_t launch_pairs_class(size_t n, hipStream_t s, const uint64_t *boards, const EvalScratch &S,
+                                     uint4 *out, const DevTables &T)
+{
+    const void *k = (const void *)eval_pairs_kernel<CLS, NT>;
+    const int lds = CLS == 0 ? PairDag<8>::lds_bytes : CLS == 1 ? PairDag<7>::lds_bytes : kClass2LdsBytes;
+    unsigned g = 0;
+    const hipError_t e = persistent_grid(k, NT, lds, n, &g);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((eval_persistent_kernel<CLS, NT>), dim3(g), dim3(NT), lds, s, boards, S.order, S.start,
-                       S.counter, out, S.global_layers, slots, T);
+    hipLaunchKernelGGL((eval_pairs_kernel<CLS, NT>), dim3(g), dim3(NT), lds, s, boards, S.order, S.start, S.counter,
+                       out, T);
     return hipGetLastError();
 }
 
-template <int CLS, int NT>
-static int class_blocks_per_cu(int lds)
+template <int NT>
+static hipError_t launch_deepest(size_t n, hipStream_t s, const uint64_t *boards, const EvalScratch &S, uint4 *out,
+                                 const DevTables &T)
 {
-    int per = 0;
-    (void)allow_lds((const void *)eval_persistent_kernel<CLS, NT>, lds);
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, (const void *)eval_persistent_kernel<CLS, NT>, NT,
-                                                     lds) != hipSuccess)
-        return 1;
-    return std::max(1, per);
+    const unsigned g = (unsigned)std::min<size_t>(n, (size_t)S.global_slots);
+    const int lds = std::max(dag_ftab_bytes(9), dag_ftab_bytes(10));
+    hipLaunchKernelGGL(eval_deepest_kernel<NT>, dim3(g), dim3(NT), lds, s, boards, S.order, S.start, S.counter, out,
+                       S.global_layers, T);
+    return hipGetLastError();
 }
 
-hipError_t launch_eval_persistent_slots(const uint64_t *boards, size_t n, uint4 *out,
-                                        const EvalScratch &S, int grid, int slots,
-                                        const DevTables &T, hipStream_t s)
+// The boards of a batch that needs no binning: as many as run at once, one
+// workgroup per CU (and per global layer slot).
+static hipError_t launch_few(const uint64_t *boards, size_t n, uint4 *out, const EvalScratch &S, int *status,
+                             const DevTables &T, hipStream_t s)
 {
-    (void)n;
+    const int lds = PairDag<8>::lds_bytes;
+    const hipError_t e = allow_lds((const void *)eval_few_kernel, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(eval_few_kernel, dim3((unsigned)n), dim3(1024), lds, s, boards, status, out, S.global_layers,
+                       T);
+    return hipGetLastError();
+}
+
+hipError_t launch_eval(const uint64_t *boards, size_t n, uint4 *out, const EvalScratch &S, int *status,
+                       const DevTables &T, hipStream_t s)
+{
+    if (n == 0) return hipSuccess;
     int dev = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
-    if (slots < 1 || slots > grid) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(zero_counter_kernel, dim3(1), dim3(64), 0, s, S.counter, 4);
-    // class 0: `grid` workgroups (two per CU: the LDS of an 8-empty root),
-    // the first `slots` of them owning a global layer slot each
-    const int lds0 = eval_class_lds_bytes(0), lds1 = eval_class_lds_bytes(1), lds2 = eval_class_lds_bytes(2);
-    e = g_class_threads[0] == 512 ? launch_class<0, 512>(grid, lds0, s, boards, S, out, slots, T)
-                                  : launch_class<0, 256>(grid, lds0, s, boards, S, out, slots, T);
+    if (n <= (size_t)std::min(cus, S.global_slots)) return launch_few(boards, n, out, S, status, T, s);
+    e = launch_eval_bin(boards, n, S, status, out, T, s);
     if (e != hipSuccess) return e;
-    if (g_class_threads[1] == 512)
-        e = launch_class<1, 512>(class_blocks_per_cu<1, 512>(lds1) * cus, lds1, s, boards, S, out, slots, T);
-    else
-        e = launch_class<1, 256>(class_blocks_per_cu<1, 256>(lds1) * cus, lds1, s, boards, S, out, slots, T);
-    if (e != hipSuccess) return e;
-    return launch_class<2, 256>(class_blocks_per_cu<2, 256>(lds2) * cus, lds2, s, boards, S, out, slots, T);
+    const bool c0 = g_class_threads[0] == 512, c1 = g_class_threads[1] == 512;
+    e = c0 ? launch_deepest<512>(n, s, boards, S, out, T) : launch_deepest<256>(n, s, boards, S, out, T);
+    if (e == hipSuccess)
+        e = c0 ? launch_pairs_class<0, 1024>(n, s, boards, S, out, T) : launch_pairs_class<0, 512>(n, s, boards, S, out, T);
+    if (e == hipSuccess)
+        e = c1 ? launch_pairs_class<1, 1024>(n, s, boards, S, out, T) : launch_pairs_class<1, 512>(n, s, boards, S, out, T);
+    if (e == hipSuccess) e = launch_pairs_class<2, kClass2Threads>(n, s, boards, S, out, T);
+    return e;
 }
 
 hipError_t launch_eval_direct(const uint64_t *boards, int n, uint4 *out, int cls,

@@ -57,6 +57,7 @@ struct EvalAlloc {
 static int eval_alloc(size_t n, int grid, hipStream_t st, EvalAlloc *A)
 {
     const size_t ints = 64;
+    grid = (int)std::min<size_t>(n, (size_t)grid);  // a layer slot per workgroup, no more of them than roots
     const size_t glayer = (size_t)grid * 2 * kDagGlobalLayer * 64;
     const size_t bytes = glayer + ints * 4 + 32 + n * 4 + n + 256;
     hipError_t e = hipMallocAsync(&A->base, bytes, st);
@@ -82,24 +83,6 @@ static int eval_alloc(size_t n, int grid, hipStream_t st, EvalAlloc *A)
 size_t eval_scratch_bytes(size_t n, int grid, bool deep)
 {
     return (deep ? (size_t)grid * 2 * kDagGlobalLayer * 64 : 0) + 64 * 4 + 32 + n * 5 + 256;
-}
-
-// Enqueue one endgame batch on st with stream-ordered scratch.
-int eval_enqueue(const uint64_t *boards, size_t n, uint4 *out, int *status, bool deep, int grid,
-                 hipStream_t st)
-{
-    DevTables T;
-    int rc = device_tables(&T);
-    if (rc) return rc;
-    EvalAlloc A;
-    rc = eval_alloc(n, deep ? grid : 0, st, &A);
-    if (rc) return rc;
-    A.S.global_slots = grid;
-    hipError_t e = launch_eval_bin(boards, n, A.S, status, out, T, st);
-    if (e == hipSuccess) e = launch_eval_persistent(boards, n, out, A.S, grid, T, st);
-    (void)hipFreeAsync(A.base, st);
-    if (e != hipSuccess) return hip_fail(e, "eval launch");
-    return 0;
 }
 
 // Enqueue one batch whose roots all belong to endgame class cls (see
@@ -145,9 +128,7 @@ int pentago_eval_batch(const pentago_board *boards, size_t n, pentago_superinfo 
     EvalAlloc A;
     rc = eval_alloc(n, grid, st, &A);
     if (rc) return rc;
-    hipError_t e = launch_eval_bin((const uint64_t *)boards, n, A.S, status, (uint4 *)out, T, st);
-    if (e == hipSuccess)
-        e = launch_eval_persistent((const uint64_t *)boards, n, (uint4 *)out, A.S, grid, T, st);
+    const hipError_t e = launch_eval((const uint64_t *)boards, n, (uint4 *)out, A.S, status, T, st);
     (void)hipFreeAsync(A.base, st);
     if (e != hipSuccess) return hip_fail(e, "eval launch");
     return 0;

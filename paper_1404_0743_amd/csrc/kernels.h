@@ -117,16 +117,14 @@ struct EvalScratch {
 
 hipError_t launch_eval_bin(const uint64_t *boards, size_t n, const EvalScratch &S, int *status,
                            uint4 *out, const DevTables &T, hipStream_t s);
-hipError_t launch_eval_persistent(const uint64_t *boards, size_t n, uint4 *out,
-                                  const EvalScratch &S, int grid, const DevTables &T,
-                                  hipStream_t s);
-// The same with only the first `slots` workgroups of class 0 owning a global
-// layer slot (1 <= slots <= grid; global_layers holds `slots` slots).
-hipError_t launch_eval_persistent_slots(const uint64_t *boards, size_t n, uint4 *out,
-                                        const EvalScratch &S, int grid, int slots,
-                                        const DevTables &T, hipStream_t s);
-// Workgroup sizes of persistent endgame classes 0 and 1 (256 or 512), set
-// by the endgame autotuner; process-wide.
+// Solve n boards: a batch no larger than the workgroups that run at once in
+// one launch, else binned by empty cells and solved by one persistent launch
+// per class (S.global_slots layer slots for roots with 9 or 10 empty cells).
+// status: incremented once per board that is invalid (its output is zero).
+hipError_t launch_eval(const uint64_t *boards, size_t n, uint4 *out, const EvalScratch &S, int *status,
+                       const DevTables &T, hipStream_t s);
+// Threads per root with 8 to 10 and with 7 empty cells (256 or 512), set by the
+// endgame autotuner; process-wide.
 void set_eval_class_threads(int c0, int c1);
 void get_eval_class_threads(int *c0, int *c1);
 hipError_t launch_eval_group(const uint64_t *boards, int e, int first, int count, uint4 *out,

@@ -99,10 +99,7 @@ int pentago_eval_batch_noalloc(const pentago_board *boards, size_t n, pentago_su
     // the binning pass clears the per-class counts and the persistent launch
     // its queue counters with small kernels: nothing from an earlier call is
     // read before it is rewritten
-    e = launch_eval_bin((const uint64_t *)boards, n, S, status, (uint4 *)out, T, st);
-    if (e == hipSuccess)
-        e = launch_eval_persistent_slots((const uint64_t *)boards, n, (uint4 *)out, S, grid,
-                                         S.global_slots, T, st);
+    e = launch_eval((const uint64_t *)boards, n, (uint4 *)out, S, status, T, st);
     if (e != hipSuccess) return hip_fail(e, "eval launch");
     return 0;
 }

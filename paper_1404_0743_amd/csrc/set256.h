@@ -402,6 +402,35 @@ PG_HD uint32_t rep_g0(uint32_t m) { return m * 0x1111u; }
 // a set of g1 values, every g0 (16-bit half)
 PG_HD uint32_t fill_g1(uint32_t m) { return spread1(m) * 0xfu; }
 
+// Where the elements of L sit inside a 32-bit word of a five-set: word
+// h2 + 2 g3 in both layouts below, with g_j = p_j + 2 h_j.
+//   PlainBits  bit g0 + 4 g1 + 16 p2, the layout of Set256
+//   SplitBits  bit p0 + 2 p1 + 4 p2 + 8 h1 + 16 h0: the low bits p_j of three
+//              dimensions side by side, h0 and h1 as the byte number (the
+//              packed endgame solver takes its words from it with a shift and
+//              a mask each)
+// set0 / set1: a 4-bit set of g0 / g1 (for p2 = 0, the other dimension 0);
+// prod: product of a g0 and a g1 set; rep0 / rep1: the same with every value
+// of the other dimension; join: the parts of p2 = 0 and p2 = 1; half: the
+// p2 = 0 or p2 = 1 part of the word where bits i, i + 1 of a g2 set are set.
+struct PlainBits {
+    static PG_HD uint32_t prod(uint32_t a, uint32_t b) { return prod16(a, b); }
+    static PG_HD uint32_t rep0(uint32_t m) { return rep_g0(m); }
+    static PG_HD uint32_t rep1(uint32_t m) { return fill_g1(m); }
+    static PG_HD uint32_t join(uint32_t lo, uint32_t hi) { return (lo & 0xffffu) | (hi << 16); }
+    static constexpr uint32_t part0 = 0x0000ffffu, part1 = 0xffff0000u;
+};
+
+struct SplitBits {
+    static PG_HD uint32_t set0(uint32_t m) { return (m & 3u) | ((m & 12u) << 14); }
+    static PG_HD uint32_t set1(uint32_t m) { return (m & 1u) | ((m & 2u) << 1) | ((m & 4u) << 6) | ((m & 8u) << 7); }
+    static PG_HD uint32_t prod(uint32_t a, uint32_t b) { return set0(a) * set1(b); }
+    static PG_HD uint32_t rep0(uint32_t m) { return set0(m) * 0x505u; }
+    static PG_HD uint32_t rep1(uint32_t m) { return set1(m) * 0x30003u; }
+    static PG_HD uint32_t join(uint32_t lo, uint32_t hi) { return lo | (hi << 4); }
+    static constexpr uint32_t part0 = 0x0f0f0f0fu, part1 = 0xf0f0f0f0u;
+};
+
 PG_HD uint32_t union_pairs6(uint32_t lo, uint32_t hi)
 {
     uint32_t s = 0;
@@ -419,72 +448,83 @@ PG_HD uint32_t union_pairs2(uint32_t lo, uint32_t hi)
 // depends on the patterns of two quadrants, and each three-quadrant line on
 // a product of two quadrants' sets with a third quadrant's; so the five-set
 // is assembled from six pair terms, each a function of two quadrants'
-// LineMasks only, already laid out as the 32-bit words of a Set256 (word
-// 2 g3 + p holds g2 = 2p in its low half and g2 = 2p + 1 in its high half,
-// g0 + 4 g1 inside a half).  A tile of entries sharing patterns can build the
-// pair terms once and assemble each entry from them.
-//   pair01 (Q0,Q1): {S01, P012, P013} each repeated in both halves, 0
-//   pair02 (Q0,Q2): E02 for p = 0, 1 (the left columns over g0, g2), and
-//                   B for p = 0, 1 (T023's Q0 set where T023's Q2 set holds g2)
-//   pair12 (Q1,Q2): E12 for p = 0, 1 (anti-diagonals over g1, g2), and
-//                   C for p = 0, 1 (T123's Q1 set where its Q2 set holds g2)
-//   pair03 (Q0,Q3): per g3, the long diagonals over g0 (both halves)
-//   pair13 (Q1,Q3): per g3, the right columns over g1 (both halves)
-//   pair23 (Q2,Q3): words 0-7: the bottom rows over g2, g3 as half-word masks;
-//                   8-9: the halves where T012's Q2 set holds g2; 10: T013's
-//                   Q3 set | T023's Q3 set << 4 | T123's Q3 set << 8; 11: 0
-PG_HD uint32_t halves(uint32_t lo, uint32_t hi) { return (lo & 0xffffu) | (hi << 16); }
-PG_HD uint32_t both_halves(uint32_t x) { return halves(x, x); }
-PG_HD uint32_t bit_halfmask(uint32_t set, int i) { return (((set >> i) & 1u) ? 0x0000ffffu : 0u) | (((set >> (i + 1)) & 1u) ? 0xffff0000u : 0u); }
-
-PG_HD uint4 pair01(const LineMasks &q0, const LineMasks &q1)
+// LineMasks only, already laid out as the 32-bit words of a set (word
+// 2 g3 + h2; B: the layout inside a word).  A tile of entries sharing
+// patterns can build the pair terms once and assemble each entry from them.
+//   pair01 (Q0,Q1): {S01, P012, P013} each for both p2, 0
+//   pair02 (Q0,Q2): E02 for h2 = 0, 1 (the left columns over g0, g2), and
+//                   B for h2 = 0, 1 (T023's Q0 set where T023's Q2 set holds g2)
+//   pair12 (Q1,Q2): E12 for h2 = 0, 1 (anti-diagonals over g1, g2), and
+//                   C for h2 = 0, 1 (T123's Q1 set where its Q2 set holds g2)
+//   pair03 (Q0,Q3): per g3, the long diagonals over g0 (both p2)
+//   pair13 (Q1,Q3): per g3, the right columns over g1 (both p2)
+//   pair23 (Q2,Q3): words 0-7: the bottom rows over g2, g3 as masks of the p2
+//                   parts; 8-9: the parts where T012's Q2 set holds g2; 10:
+//                   T013's Q3 set | T023's Q3 set << 4 | T123's Q3 set << 8; 11: 0
+template <class B>
+PG_HD uint32_t both_parts(uint32_t x) { return B::join(x, x); }
+template <class B>
+PG_HD uint32_t part_mask(uint32_t set, int i)
 {
-    const uint32_t S01 = union_pairs6(q0.a, q1.a);
-    const uint32_t P012 = prod16(nib(q0.c, 4), nib(q1.c, 4));
-    const uint32_t P013 = prod16(nib(q0.c, 2), nib(q1.c, 2));
-    return make_uint4(both_halves(S01), both_halves(P012), both_halves(P013), 0u);
+    return (((set >> i) & 1u) ? B::part0 : 0u) | (((set >> (i + 1)) & 1u) ? B::part1 : 0u);
 }
 
+template <class B = PlainBits>
+PG_HD uint4 pair01(const LineMasks &q0, const LineMasks &q1)
+{
+    uint32_t S01 = 0;
+#pragma unroll
+    for (int i = 0; i < 6; i++) S01 |= B::prod(nib(q0.a, i), nib(q1.a, i));
+    const uint32_t P012 = B::prod(nib(q0.c, 4), nib(q1.c, 4));
+    const uint32_t P013 = B::prod(nib(q0.c, 2), nib(q1.c, 2));
+    return make_uint4(both_parts<B>(S01), both_parts<B>(P012), both_parts<B>(P013), 0u);
+}
+
+template <class B = PlainBits>
 PG_HD uint4 pair02(const LineMasks &q0, const LineMasks &q2)
 {
     const uint32_t S02 = union_pairs6(q0.b, q2.b);  // g0 + 4 g2
-    const uint32_t b0 = rep_g0(nib(q0.c, 3)), b2 = nib(q2.c, 3);
+    const uint32_t b0 = B::rep0(nib(q0.c, 3)), b2 = nib(q2.c, 3);
     uint32_t e[2], b[2];
 #pragma unroll
     for (int p = 0; p < 2; p++) {
-        e[p] = halves(rep_g0(nib(S02, 2 * p)), rep_g0(nib(S02, 2 * p + 1)));
-        b[p] = halves(((b2 >> (2 * p)) & 1u) ? b0 : 0u, ((b2 >> (2 * p + 1)) & 1u) ? b0 : 0u);
+        e[p] = B::join(B::rep0(nib(S02, 2 * p)), B::rep0(nib(S02, 2 * p + 1)));
+        b[p] = B::join(((b2 >> (2 * p)) & 1u) ? b0 : 0u, ((b2 >> (2 * p + 1)) & 1u) ? b0 : 0u);
     }
     return make_uint4(e[0], e[1], b[0], b[1]);
 }
 
+template <class B = PlainBits>
 PG_HD uint4 pair12(const LineMasks &q1, const LineMasks &q2)
 {
     const uint32_t S12 = union_pairs2(q1.c, q2.c);  // g1 + 4 g2
-    const uint32_t c1 = fill_g1(nib(q1.c, 5)), c2 = nib(q2.c, 5);
+    const uint32_t c1 = B::rep1(nib(q1.c, 5)), c2 = nib(q2.c, 5);
     uint32_t e[2], c[2];
 #pragma unroll
     for (int p = 0; p < 2; p++) {
-        e[p] = halves(fill_g1(nib(S12, 2 * p)), fill_g1(nib(S12, 2 * p + 1)));
-        c[p] = halves(((c2 >> (2 * p)) & 1u) ? c1 : 0u, ((c2 >> (2 * p + 1)) & 1u) ? c1 : 0u);
+        e[p] = B::join(B::rep1(nib(S12, 2 * p)), B::rep1(nib(S12, 2 * p + 1)));
+        c[p] = B::join(((c2 >> (2 * p)) & 1u) ? c1 : 0u, ((c2 >> (2 * p + 1)) & 1u) ? c1 : 0u);
     }
     return make_uint4(e[0], e[1], c[0], c[1]);
 }
 
+template <class B = PlainBits>
 PG_HD uint4 pair03(const LineMasks &q0, const LineMasks &q3)
 {
     const uint32_t S03 = union_pairs2(q0.c, q3.c);  // g0 + 4 g3
-    return make_uint4(both_halves(rep_g0(nib(S03, 0))), both_halves(rep_g0(nib(S03, 1))),
-                      both_halves(rep_g0(nib(S03, 2))), both_halves(rep_g0(nib(S03, 3))));
+    return make_uint4(both_parts<B>(B::rep0(nib(S03, 0))), both_parts<B>(B::rep0(nib(S03, 1))),
+                      both_parts<B>(B::rep0(nib(S03, 2))), both_parts<B>(B::rep0(nib(S03, 3))));
 }
 
+template <class B = PlainBits>
 PG_HD uint4 pair13(const LineMasks &q1, const LineMasks &q3)
 {
     const uint32_t S13 = union_pairs6(q1.b, q3.b);  // g1 + 4 g3
-    return make_uint4(both_halves(fill_g1(nib(S13, 0))), both_halves(fill_g1(nib(S13, 1))),
-                      both_halves(fill_g1(nib(S13, 2))), both_halves(fill_g1(nib(S13, 3))));
+    return make_uint4(both_parts<B>(B::rep1(nib(S13, 0))), both_parts<B>(B::rep1(nib(S13, 1))),
+                      both_parts<B>(B::rep1(nib(S13, 2))), both_parts<B>(B::rep1(nib(S13, 3))));
 }
 
+template <class B = PlainBits>
 PG_HD void pair23(const LineMasks &q2, const LineMasks &q3, uint4 out[3])
 {
     const uint32_t S23 = union_pairs6(q2.a, q3.a);  // g2 + 4 g3
@@ -492,10 +532,10 @@ PG_HD void pair23(const LineMasks &q2, const LineMasks &q3, uint4 out[3])
 #pragma unroll
     for (int g3 = 0; g3 < 4; g3++)
 #pragma unroll
-        for (int p = 0; p < 2; p++) w[2 * g3 + p] = bit_halfmask(S23, 2 * p + 4 * g3);
+        for (int p = 0; p < 2; p++) w[2 * g3 + p] = part_mask<B>(S23, 2 * p + 4 * g3);
     const uint32_t a2 = nib(q2.c, 4);
-    w[8] = bit_halfmask(a2, 0);
-    w[9] = bit_halfmask(a2, 2);
+    w[8] = part_mask<B>(a2, 0);
+    w[9] = part_mask<B>(a2, 2);
     w[10] = nib(q3.c, 2) | (nib(q3.c, 3) << 4) | (nib(q3.c, 5) << 8);
     w[11] = 0;
     out[0] = make_uint4(w[0], w[1], w[2], w[3]);
@@ -530,13 +570,16 @@ PG_HD Set256 five_assemble(const uint4 &t01, const uint4 &t02, const uint4 &t12,
     return r;
 }
 
-// The five-set of one colour from the line masks of its four quadrants.
+// The five-set of one colour from the line masks of its four quadrants (B:
+// the layout of its words).
+template <class B = PlainBits>
 PG_HD Set256 five_set(const LineMasks &q0, const LineMasks &q1, const LineMasks &q2,
                       const LineMasks &q3)
 {
     uint4 t23[3];
-    pair23(q2, q3, t23);
-    return five_assemble(pair01(q0, q1), pair02(q0, q2), pair12(q1, q2), pair03(q0, q3), pair13(q1, q3), t23);
+    pair23<B>(q2, q3, t23);
+    return five_assemble(pair01<B>(q0, q1), pair02<B>(q0, q2), pair12<B>(q1, q2), pair03<B>(q0, q3),
+                         pair13<B>(q1, q3), t23);
 }
 
 // ------------------------------------------------------------------------
