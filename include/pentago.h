@@ -345,7 +345,7 @@ int pentago_eval_batch_noalloc(const pentago_board *boards, size_t n, pentago_su
  * solved layer by layer across the whole GPU, two layers at a time in HBM.
  *   out   device, 64 B.
  * Device scratch (two layers of 64 B records, 2 x max_t C(e,t) C(t,ceil(t/2))
- * x 64 B, plus the five-set table: 2.2 GB for e = 18, 17.0 GB for e = 20) is
+ * x 64 B, plus 264 B per subset of the cells: 2.3 GB for e = 18, 17.3 GB for e = 20) is
  * allocated stream-ordered on hip_stream and released after the call's work.  Stream-ordered and asynchronous.  EINVAL for invalid codes or
  * stone counts; ERANGE for more than 20 empty cells; EDEVICE when the scratch
  * allocation fails. */

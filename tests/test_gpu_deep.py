@@ -286,3 +286,15 @@ def test_errors(P):
     with pytest.raises(P.PentagoError) as e:
         P.pentago_eval_deep(P.boards_to_codes(b.reshape(1, 36))[0], out)
     assert e.value.code == P.ERANGE
+
+
+@pytest.mark.parametrize("e", [11, 13, 17, 19, 20])
+def test_full_table_blocks_match_parity_halves(P, e):
+    """The whole-table solver reads its children block by block, staged in LDS
+    up to 18 empty cells and from memory beyond (19 and 20: some blocks are
+    larger than LDS), with one or several blocks to a workgroup; the two
+    parity halves, solved the plain way, together give the same table."""
+    b = I.random_play_boards(1, 36 - e, 36 - e, seed=90 + e)[0]
+    log("deep blocks, empties", e)
+    full = deep(P, b)
+    assert np.array_equal(deep_parity(P, b, 0) | deep_parity(P, b, 1), full)
