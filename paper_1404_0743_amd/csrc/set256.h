@@ -56,7 +56,14 @@ PG_HD uint32_t rotr32(uint32_t x, int s) { return (x >> s) | (x << (32 - s)); }
 PG_HD uint32_t bfi(uint32_t m, uint32_t a, uint32_t b) { return (m & a) | (~m & b); }
 
 // swap the two bytes of each 16-bit half
-PG_HD uint32_t swap_bytes16(uint32_t x) { return ((x >> 8) & 0x00ff00ffu) | ((x << 8) & 0xff00ff00u); }
+PG_HD uint32_t swap_bytes16(uint32_t x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return (uint32_t)__builtin_amdgcn_perm(x, x, 0x02030001u);
+#else
+    return ((x >> 8) & 0x00ff00ffu) | ((x << 8) & 0xff00ff00u);
+#endif
+}
 
 // rmin(X)(g) = AND over the 8 single-quadrant turns r of X(g + r), so that
 // rmax(X) = not rmin(not X) (Section III's rmax, by De Morgan).  Along each
@@ -66,32 +73,57 @@ PG_HD uint32_t swap_bytes16(uint32_t x) { return ((x >> 8) & 0x00ff00ffu) | ((x 
 //   dimension 0 (bit pairs inside nibbles), dimension 1 (nibbles inside
 //   16-bit halves), dimension 2 (halves and the two words of a pair),
 //   dimension 3 (word pairs).
-PG_HD Set256 rmin(const Set256 &x)
+//
+// The terms of all four dimensions, ANDed up to the last step: rmin(x).w[w] =
+// q[w] & m3[..].  Written with one three-input operation where two ANDs would
+// be (bitop3): 14 VALU instructions a word, 17 with ANDs and shifts alone.
+PG_HD uint32_t and3w(uint32_t a, uint32_t b, uint32_t c)
 {
-    Set256 r;
+#if defined(__HIP_DEVICE_COMPILE__)
+    return (uint32_t)__builtin_amdgcn_bitop3_b32(a, b, c, 0x80);
+#else
+    return a & b & c;
+#endif
+}
+
+struct RminTerms {
+    uint32_t q[8], m3[4];
+};
+
+PG_HD RminTerms rmin_terms(const Set256 &x)
+{
+    RminTerms r;
     uint32_t m2[4];
 #pragma unroll
     for (int g3 = 0; g3 < 4; g3++) m2[g3] = rotr32(x.w[2 * g3] & x.w[2 * g3 + 1], 16);
-    uint32_t m3[4];
 #pragma unroll
     for (int p = 0; p < 2; p++) {
-        m3[p] = x.w[2 + p] & x.w[6 + p];      // neighbours of g3 = 0 and 2
-        m3[2 + p] = x.w[0 + p] & x.w[4 + p];  // neighbours of g3 = 1 and 3
+        r.m3[p] = x.w[2 + p] & x.w[6 + p];      // neighbours of g3 = 0 and 2
+        r.m3[2 + p] = x.w[0 + p] & x.w[4 + p];  // neighbours of g3 = 1 and 3
     }
 #pragma unroll
     for (int w = 0; w < 8; w++) {
-        const int g3 = w >> 1, p = w & 1;
-        const uint32_t u = x.w[w];
-        // dimension 0: P holds (u0 & u2, u1 & u3) in bits 0, 1 of each nibble
-        const uint32_t P = u & (u >> 2) & 0x33333333u;
-        const uint32_t Q = ((P >> 1) & 0x11111111u) | ((P << 1) & 0x22222222u);
-        const uint32_t n0 = Q | (Q << 2);
-        // dimension 1: the same one level up, nibbles inside each half
-        const uint32_t P1 = u & (u >> 8) & 0x00ff00ffu;
-        const uint32_t Q1 = ((P1 >> 4) & 0x000f000fu) | ((P1 << 4) & 0x00f000f0u);
-        const uint32_t n1 = Q1 | (Q1 << 8);
-        r.w[w] = (n0 & n1) & (m2[g3] & m3[(g3 & 1) * 2 + p]);
+        const uint32_t u = x.w[w], t = u >> 2;
+        // dimension 0: the ANDs of values 0, 2 (bit 0 of a nibble) and 1, 3
+        // (bit 1) trade places, then fill the nibble
+        const uint32_t e02 = and3w(u, t, 0x11111111u), e13 = and3w(u, t, 0x22222222u);
+        const uint32_t e = (e02 << 1) | (e13 >> 1);
+        const uint32_t n0 = e | (e << 2);
+        // dimension 1: each nibble with the one two places on in its half (the
+        // other byte), then the nibbles of a byte trade places
+        const uint32_t y = u & swap_bytes16(u);
+        const uint32_t n1 = bfi(0x0f0f0f0fu, y >> 4, y << 4);
+        r.q[w] = and3w(n0, n1, m2[w >> 1]);
     }
+    return r;
+}
+
+PG_HD Set256 rmin(const Set256 &x)
+{
+    const RminTerms t = rmin_terms(x);
+    Set256 r;
+#pragma unroll
+    for (int w = 0; w < 8; w++) r.w[w] = t.q[w] & t.m3[((w >> 1) & 1) * 2 + (w & 1)];
     return r;
 }
 
@@ -606,12 +638,12 @@ PG_HD void child_terms(const Set256 &Fparent_t, const Set256 &Wt, const Set256 &
                        Set256 &B)
 {
     // rmax(not X) = not rmin(X)
-    const Set256 a = rmin(Nt);
-    const Set256 b = rmin(Wt);
+    const RminTerms a = rmin_terms(Nt), b = rmin_terms(Wt);
 #pragma unroll
     for (int i = 0; i < 8; i++) {
-        A.w[i] = Fparent_t.w[i] | ~a.w[i];
-        B.w[i] = Fparent_t.w[i] | ~b.w[i];
+        const int m = ((i >> 1) & 1) * 2 + (i & 1);
+        A.w[i] = Fparent_t.w[i] | ~(a.q[i] & a.m3[m]);
+        B.w[i] = Fparent_t.w[i] | ~(b.q[i] & b.m3[m]);
     }
 }
 
