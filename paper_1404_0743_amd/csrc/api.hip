@@ -261,20 +261,19 @@ int make_job(const pentago_section &s, const pentago_superinfo *const child[4],
     J->o1 = o[0];
     J->o2 = o[1];
     const int cmd = (J->emask >> J->d) & 1 ? J->cm[J->d] : 0;
-    // lines per tile: at most 8 (one 8^4 block row), the child items of a
-    // tile in one pass of its 256 threads when the child line allows, and the
-    // tile's LDS within 64 KiB
+    // lines per tile: at most 8 (one 8^4 block row), the tile's LDS within 40
+    // KiB, so that four 512-thread workgroups share a CU, and a contiguous range
+    // of tiles per XCD.  Timed against every shape over 36 sections of 33 to 35
+    // stones and 3,000 to 12 million entries: 1.06 of the best shape's time in
+    // the mean, 1.37 at worst (32 KiB 1.09, 52 KiB 1.08, 256 threads 1.09 at
+    // their best cap; 256 threads and 64 KiB, the rule before, 1.25 and 1.73)
     int G = 8;
     const TileShape tuned = tuned_tile_shape(*J);
-    J->threads = force_threads > 0 ? force_threads : tuned.lines > 0 ? tuned.threads : 256;
-    J->order = force_order >= 0 ? force_order : tuned.lines > 0 ? tuned.order : 0;
+    J->threads = force_threads > 0 ? force_threads : tuned.lines > 0 ? tuned.threads : 512;
+    J->order = force_order >= 0 ? force_order : tuned.lines > 0 ? tuned.order : 1;
     if (forceG > 0) G = forceG;
     else if (tuned.lines > 0) G = tuned.lines;
-    else {
-        // (the kernels give every line 8 slots per position when D == 3,
-        // so a smaller G only helps the child pass for D == 3)
-        while (G > 1 && sweep_lds_bytes(G, J->m[J->d], cmd) > 65536) G--;
-    }
+    else while (G > 1 && sweep_lds_bytes(G, J->m[J->d], cmd) > 40960) G--;
     J->G = G;
     J->ngroups = (J->m[J->e] + G - 1) / G;
     J->ntiles = (long long)J->m[J->o1] * J->m[J->o2] * J->ngroups;

@@ -94,19 +94,18 @@ static int plan_build(const pentago_section_job *jobs, size_t n, hipStream_t str
             if (((J[i].emask >> j) & 1) &&
                 (dl < 0 || J[i].m[j] > J[i].m[dl] || (J[i].m[j] == J[i].m[dl] && J[i].cm[j] > J[i].cm[dl])))
                 dl = j;
-        if (dl >= 0 && dl != J[i].d) {
+        if (dl < 0) dl = J[i].d;
+        if (dl != J[i].d) {
             rc = make_job(jobs[i].section, jobs[i].child, jobs[i].out, &J[i], dl, 0);
             if (rc) return rc;
         }
-        // a launch's occupancy follows its largest tile's LDS: keep every
-        // tile within the cap by taking fewer lines per tile
-        if (J[i].lds_bytes > lds_cap && J[i].G > 1) {
-            int G = J[i].G;
-            const int cmd = (J[i].emask >> J[i].d) & 1 ? J[i].cm[J[i].d] : 0;
-            while (G > 1 && sweep_lds_bytes(G, J[i].m[J[i].d], cmd) > lds_cap) G--;
-            rc = make_job(jobs[i].section, jobs[i].child, jobs[i].out, &J[i], J[i].d, G);
-            if (rc) return rc;
-        }
+        // a launch's occupancy follows its largest tile's LDS: as many lines
+        // per tile (at most 8, or the section's tuned number) as the cap holds
+        const int cmd = (J[i].emask >> dl) & 1 ? J[i].cm[dl] : 0, tuned = tuned_tile_shape(J[i]).lines;
+        int G = tuned > 0 ? tuned : 8;
+        while (G > 1 && sweep_lds_bytes(G, J[i].m[dl], cmd) > lds_cap) G--;
+        rc = make_job(jobs[i].section, jobs[i].child, jobs[i].out, &J[i], dl, G);
+        if (rc) return rc;
         if (reps) set_child_syms(jobs[i].section, jobs[i].child, &J[i]);
         rc = validate_children(J[i], stream);
         if (rc) return rc;
