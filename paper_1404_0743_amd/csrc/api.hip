@@ -75,7 +75,7 @@ int device_tables(DevTables *out)
         size_t bytes;
         void **dst;
     };
-    void *canon, *qinfo, *lm, *dn, *dr, *sel, *cref, *uref, *smask, *srank, *symmap, *symcode, *syminv, *dedge, *plm, *psel, *pch;
+    void *canon, *qinfo, *lm, *dn, *dr, *sel, *cref, *uref, *smask, *srank, *symmap, *symcode, *syminv, *dedge, *plm, *psel, *pch, *rorder, *rstart;
     Up ups[] = {{H.canon.data(), H.canon.size() * 2, &canon},
                 {H.qinfo.data(), H.qinfo.size() * sizeof(QInfo), &qinfo},
                 {H.lm.data(), H.lm.size() * sizeof(LineMasks), &lm},
@@ -92,6 +92,8 @@ int device_tables(DevTables *out)
                 {H.pat_lm.data(), H.pat_lm.size() * sizeof(LineMasks), &plm},
                 {H.pat_sel.data(), H.pat_sel.size() * 4, &psel},
                 {H.pat_child.data(), H.pat_child.size() * sizeof(PosChild), &pch},
+                {H.run_order.data(), H.run_order.size() * 4, &rorder},
+                {H.run_start.data(), H.run_start.size() * 2, &rstart},
                 {edges.data(), edges.size() * 2, &dedge}};
     for (Up &u : ups) {
         e = hipMalloc(&p, u.bytes);
@@ -117,6 +119,8 @@ int device_tables(DevTables *out)
     T.pat_lm = (const LineMasks *)plm;
     T.pat_sel = (const uint4 *)psel;
     T.pat_child = (const PosChild *)pch;
+    T.run_order = (const uint32_t *)rorder;
+    T.run_start = (const uint16_t *)rstart;
     g_dev_tables[dev] = T;
     *out = T;
     return 0;
@@ -279,7 +283,73 @@ int make_job(const pentago_section &s, const pentago_superinfo *const child[4],
     J->ntiles = (long long)J->m[J->o1] * J->m[J->o2] * J->ngroups;
     J->lds_bytes = sweep_lds_bytes(G, J->m[J->d], cmd);
     J->out = (uint4 *)out;
+    J->fam = -1;
     return 0;
+}
+
+// Small sections go in tiles of sibling lines, unless tiles of lines were tuned
+// to be faster: they save the prep launch and its scratch (25,000 entries: 9 us
+// against 28; 0.14 million 19 against 34, 0.9 million 51 against 64).  Beyond a
+// million entries the prep launch no longer shows, and tiles of lines, more
+// parents to a table, are as fast or faster (4 to 12 million entries: 0.74 to
+// 1.26 of the siblings' time, 0.96 in the mean).  The two staged children must
+// be held as themselves.
+void take_siblings(const pentago_section &s, SweepJob *J)
+{
+    const TileShape tuned = tuned_tile_shape(*J);
+    uint64_t entries = 1;
+    for (int j = 0; j < 4; j++) entries *= (uint64_t)J->m[j];
+    if (tuned.lines > 0 ? !tuned.runs : entries > (1u << 20)) return;
+    SweepJob R = *J;
+    if (make_run(s, &R, kRunLdsCap) && !R.csym[R.d] && !R.csym[R.fam]) *J = R;
+}
+
+// Lay J out in tiles of sibling lines if its section has empty cells in two
+// quadrants or more and one of them (besides the staged one) has a single
+// empty cell in every pattern: dimensions d and fam, tiles and LDS.  False, and J
+// as it was, if no such layout fits.
+bool make_run(const pentago_section &s, SweepJob *J, int lds_cap)
+{
+    const HostTables &H = host_tables();
+    if (J->odmask) return false;  // 35 stones: one quadrant only
+    int empt[4], d = -1, f = -1;
+    for (int j = 0; j < 4; j++) empt[j] = 9 - s.black[j] - s.white[j];
+    // lines along the quadrant with the most empty cells (its children are
+    // many to a pattern), the longest of them; then the siblings along the
+    // quadrant with the most child entries to prepare otherwise
+    // (lines along dimension 3 or 2 save most of the two layout changes of
+    // every entry, 80 instructions of a parent's 400 along 0 or 1)
+    auto len = [&](int j) { return J->m[j] * (j == 3 ? 5 : j == 2 ? 5 : 4); };
+    for (int j = 0; j < 4; j++)
+        if (empt[j] && (d < 0 || empt[j] > empt[d] || (empt[j] == empt[d] && len(j) >= len(d)))) d = j;
+    for (int j = 0; j < 4; j++)
+        if (j != d && empt[j] == 1 && (f < 0 || (long long)J->cm[j] * J->m[f] > (long long)J->cm[f] * J->m[j])) f = j;
+    if (d < 0 || f < 0) return false;
+    const int cls = H.class_number[s.black[f]][s.white[f]];
+    for (int cap = 0; cap < kRunCaps; cap++) {
+        const RunClass &R = H.runs[cap][J->mover - 1][cls];
+        const int lds = sweep_run_lds_bytes(R.max_patterns, R.max_children, J->m[d], J->cm[d]);
+        if (lds > (cap + 1 < kRunCaps ? lds_cap : 65536)) continue;
+        int o[2], n = 0;
+        for (int j = 0; j < 4; j++)
+            if (j != d && j != f) o[n++] = j;
+        const long long tiles = (long long)R.count * J->m[o[0]] * J->m[o[1]];
+        if (tiles > 0x7fffffffLL) return false;
+        J->d = d;
+        J->fam = f;
+        J->nchd = empt[d];
+        J->o1 = o[0];
+        J->o2 = o[1];
+        J->frun = R.start;
+        J->fruns = R.count;
+        J->flines = R.max_patterns;
+        J->fkids = R.max_children;
+        J->ntiles = tiles;
+        J->lds_bytes = lds;
+        J->threads = 512;
+        return true;
+    }
+    return false;
 }
 
 size_t prep_bytes(const SweepJob &J, int j)
@@ -359,6 +429,7 @@ int pentago_solve_section(pentago_section s, const pentago_superinfo *const chil
     SweepJob J;
     rc = make_job(s, child, out, &J, -1, 0);
     if (rc) return rc;
+    take_siblings(s, &J);
     rc = validate_children(J, (hipStream_t)hip_stream);
     if (rc) return rc;
     return run_job(J, T, (hipStream_t)hip_stream);

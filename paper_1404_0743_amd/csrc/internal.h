@@ -30,12 +30,18 @@ int run_job(SweepJob &J, const DevTables &T, hipStream_t st);
 // With pentago_set_validate(1): EINVAL unless every child table J reads has
 // each entry's win set inside its not-lose set (synchronises st); else 0.
 int validate_children(const SweepJob &J, hipStream_t st);
-// Tile shape of a section geometry chosen by the autotuner (0 lines: none).
+// Tile shape of a section geometry chosen by the autotuner (0 lines: none);
+// runs: tiles of sibling lines (make_run) were faster than the best of these.
 struct TileShape {
     int lines;
     int threads;
     int order;
+    bool runs;
 };
+constexpr int kRunLdsCap = 53248;  // LDS of a tile of sibling lines: three workgroups per CU
+bool make_run(const pentago_section &s, SweepJob *J, int lds_cap);
+// make_run where it is the faster layout (after set_child_syms, if that is used)
+void take_siblings(const pentago_section &s, SweepJob *J);
 TileShape tuned_tile_shape(const SweepJob &J);
 void remember_tile_shape(const SweepJob &J, TileShape t);
 pentago_section section_image(const pentago_section &s, int sym);

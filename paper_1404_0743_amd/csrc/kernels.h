@@ -35,6 +35,8 @@ struct DevTables {
     const LineMasks *pat_lm;    // per-pattern lookups of the tile set-up (HostTables)
     const uint4 *pat_sel;
     const PosChild *pat_child;
+    const uint32_t *run_order;  // runs of patterns by their child (HostTables)
+    const uint16_t *run_start;
 };
 
 // The table of the image section sym(s) from the table of s (Section III,
@@ -76,6 +78,10 @@ struct SweepJob {
     int lds_bytes;     // dynamic LDS needed by one tile
     int threads;       // workgroup size of the one-section sweep (256 or 512)
     int order;         // tile order of the one-section sweep (0 natural, 1 by XCD)
+    // Tiles of sibling lines (sweep_run_tile): the second staged quadrant, whose
+    // patterns have one empty cell (-1: none), the first of its class's runs in
+    // run_start, their number, and the most lines and child lines of one.
+    int fam, frun, fruns, flines, fkids;
     // Children held as their representatives under the board symmetries:
     // child[j] is then the table of a section whose image under symmetry
     // csym[j] is child j (0: child[j] is child j itself); rm[j] is that
@@ -150,6 +156,9 @@ hipError_t launch_lookup(const uint64_t *boards, const int *sec_of, int n,
 // Dynamic LDS of one sweep tile: G lines of mD parents, child lines of cmD
 // entries (cmD = 0 when the staged dimension has no children).
 int sweep_lds_bytes(int G, int mD, int cmD);
+// The same for a tile of sibling lines: G lines, F child lines of the second
+// staged quadrant.
+int sweep_run_lds_bytes(int G, int F, int mD, int cmD);
 
 // Nodes of the largest layer of any supported root (10 empty cells).
 constexpr int kDagGlobalLayer = 4200;

@@ -345,6 +345,89 @@ int sweep_lds_bytes(int G, int mD, int cmD)
     return tile_lds_bytes(G, mD, cmD, nullptr, nullptr);
 }
 
+// Store a parent's sets (internal layout): lane 4 q + l4 of the wave holds
+// parent 16 l4 + q of the 64 from g0 (n in all), at position iD of the line
+// with offset coefficients lc.  After the quad transpose store p writes parents
+// 16 p .. 16 p + 15.
+template <int D>
+__device__ __forceinline__ void store_parent(const SweepJob &J, const uint4 lc, Set256 &W, Set256 &N, int iD, int g0, int n,
+                                             int l4, int q)
+{
+    swap_with3<D>(W);
+    swap_with3<D>(N);
+    uint4 r[4] = {make_uint4(W.w[0], W.w[1], W.w[2], W.w[3]), make_uint4(W.w[4], W.w[5], W.w[6], W.w[7]),
+                  make_uint4(N.w[0], N.w[1], N.w[2], N.w[3]), make_uint4(N.w[4], N.w[5], N.w[6], N.w[7])};
+    quad_transpose(r, l4);
+    const uint32_t bD = (uint32_t)iD >> 3;
+    const uint32_t sD = min(8u, (uint32_t)J.m[D] - 8u * bD), rD = (uint32_t)iD & 7u;
+    // for D = 3 every coefficient but c0 is below 2^13 (products of block
+    // extents), so 24-bit multiplies are exact
+    const uint32_t off = D == 3 ? lc.x + __umul24(lc.y, bD) + __umul24(lc.z, sD) + rD
+                                : lc.x + lc.y * bD + lc.z * sD + lc.w * rD;
+    const uint32_t offs[4] = {quad_perm<0x00>(off), quad_perm<0x55>(off), quad_perm<0xAA>(off), quad_perm<0xFF>(off)};
+#pragma unroll
+    for (int p = 0; p < 4; p++)
+        if (g0 + 16 * p + q < n) store_stream(J.out + 4 * offs[p] + l4, r[p]);
+}
+
+// The references of partial-set item it (see line_tables): chunk slots carry
+// two (0xffff: unused slot), the lines missing D three.
+template <int D>
+__device__ __forceinline__ uint32_t partial_refs(const DevTables &T, int it)
+{
+    const int l = it - 33 * (int)(((uint32_t)it * 1986u) >> 16);
+    return l < 18 ? (uint32_t)T.chunk_ref[D * 18 + l] | 0xff0000u : T.u_ref[D * 15 + (l - 18)];
+}
+
+// The partial sets and chunk tables of n sets of four LineMasks (a line and a
+// colour each) by the whole workgroup; slot 18 of every set's O is zero
+// before, refs0 are the references of this thread's first item.  lut(vx): the
+// 192 entries of set vx.  Ends with a barrier.
+template <int D, class Lut>
+__device__ __forceinline__ void line_tables(const DevTables &T, const LineMasks *lmq_all, uint2 *O_all, int n,
+                                            uint32_t refs0, Lut lut)
+{
+    // partial sets: item (set, l) for the 18 chunk slots and the 15 lines
+    // missing D (ORed into U); it / 33 by a 16-bit reciprocal, exact for it <
+    // 33 * 32
+    for (int it = threadIdx.x; it < n * 33; it += blockDim.x) {
+        const int vx = (int)(((uint32_t)it * 1986u) >> 16), l = it - 33 * vx;
+        const LineMasks *lmq = lmq_all + 4 * vx;
+        const uint32_t refs = it == (int)threadIdx.x ? refs0 : partial_refs<D>(T, it);
+        uint2 pr = ref_product3<D>(lmq, refs);
+        if (l < 18) {
+            if ((refs & 0xffffu) == 0xffffu) pr = make_uint2(0, 0);
+            O_all[kOSlots * vx + l] = pr;
+        } else {
+            uint32_t *u = (uint32_t *)(O_all + kOSlots * vx + 18);
+            if (pr.x) atomicOr(u, pr.x);
+            if (pr.y) atomicOr(u + 1, pr.y);
+        }
+    }
+    __syncthreads();
+    // chunk tables: item (set, chunk, subset s of the chunk's first 5 lines)
+    // writes entries s and s + 32 (the 6th line added); 32 consecutive lanes
+    // write 32 consecutive entries
+    for (int it = threadIdx.x; it < n * 3 * 32; it += blockDim.x) {
+        const int sigma = it & 31, g = it >> 5, vx = g / 3, ch = g - 3 * vx;
+        const uint2 *O = O_all + kOSlots * vx + 6 * ch;
+        uint2 r = ch == 0 ? O_all[kOSlots * vx + 18] : make_uint2(0, 0);
+#pragma unroll
+        for (int b = 0; b < 5; b++) {
+            if ((sigma >> b) & 1) {
+                const uint2 o = O[b];
+                r.x |= o.x;
+                r.y |= o.y;
+            }
+        }
+        uint2 *dst = lut(vx) + 64 * ch + sigma;
+        const uint2 o5 = O[5];
+        dst[0] = r;
+        dst[32] = make_uint2(r.x | o5.x, r.y | o5.y);
+    }
+    __syncthreads();
+}
+
 // SYMC: the staged child is held as its representative (J.csym[D] != 0).
 // STAGED: quadrant D has empty cells (every section but full boards, which
 // the one-section sweep hands to the terminal kernel; only the batched forms
@@ -383,13 +466,7 @@ __device__ __forceinline__ void sweep_tile(const SweepJob &J, const DevTables &T
 
     // The line references of this thread's first partial-set item (below)
     // are fetched now, so that their latency overlaps phase 0.
-    auto item_refs = [&](int it) -> uint32_t {
-        const int l = it - 33 * (int)(((uint32_t)it * 1986u) >> 16);
-        // chunk slots carry two references (0xffff: unused slot), the lines
-        // missing D three
-        return l < 18 ? (uint32_t)T.chunk_ref[D * 18 + l] | 0xff0000u : T.u_ref[D * 15 + (l - 18)];
-    };
-    const uint32_t refs0 = (int)threadIdx.x < nlines * 2 * 33 ? item_refs(threadIdx.x) : 0u;
+    const uint32_t refs0 = (int)threadIdx.x < nlines * 2 * 33 ? partial_refs<D>(T, threadIdx.x) : 0u;
 
     // The first child item of this thread is fetched from HBM now, so its
     // latency overlaps the table set-up below.
@@ -449,45 +526,8 @@ __device__ __forceinline__ void sweep_tile(const SweepJob &J, const DevTables &T
         }
     }
     __syncthreads();
-    // partial sets: item (line, colour, l) for the 18 chunk slots and the 15
-    // lines missing D (ORed into U); it / 33 by a 16-bit reciprocal, exact
-    // for it < 33 * 16
-    for (int it = threadIdx.x; it < nlines * 2 * 33; it += blockDim.x) {
-        const int vx = (int)(((uint32_t)it * 1986u) >> 16), l = it - 33 * vx;
-        const LineMasks *lmq = L.lmq + 4 * vx;
-        const uint32_t refs = it == (int)threadIdx.x ? refs0 : item_refs(it);
-        uint2 pr = ref_product3<D>(lmq, refs);
-        if (l < 18) {
-            if ((refs & 0xffffu) == 0xffffu) pr = make_uint2(0, 0);
-            L.O[kOSlots * vx + l] = pr;
-        } else {
-            uint32_t *u = (uint32_t *)(L.O + kOSlots * vx + 18);
-            if (pr.x) atomicOr(u, pr.x);
-            if (pr.y) atomicOr(u + 1, pr.y);
-        }
-    }
-    __syncthreads();
-    // chunk tables: item (line, colour, chunk, subset s of the chunk's first
-    // 5 lines) writes entries s and s + 32 (the 6th line added); 32
-    // consecutive lanes write 32 consecutive entries
-    for (int it = threadIdx.x; it < nlines * 2 * 3 * 32; it += blockDim.x) {
-        const int sigma = it & 31, g = it >> 5, vx = g / 3, ch = g - 3 * vx;
-        const uint2 *O = L.O + kOSlots * vx + 6 * ch;
-        uint2 r = ch == 0 ? L.O[kOSlots * vx + 18] : make_uint2(0, 0);
-#pragma unroll
-        for (int b = 0; b < 5; b++) {
-            if ((sigma >> b) & 1) {
-                const uint2 o = O[b];
-                r.x |= o.x;
-                r.y |= o.y;
-            }
-        }
-        uint2 *dst = L.lut + kLutStride * (vx >> 1) + 192 * (vx & 1) + 64 * ch + sigma;
-        const uint2 o5 = O[5];
-        dst[0] = r;
-        dst[32] = make_uint2(r.x | o5.x, r.y | o5.y);
-    }
-    __syncthreads();
+    line_tables<D>(T, L.lmq, L.O, 2 * nlines, refs0,
+                   [&](int vx) { return L.lut + kLutStride * (vx >> 1) + 192 * (vx & 1); });
 
     // Phase 1: stage the child line(s) of dimension D (Fig. 3 "gather"):
     // A = F_c(child) | rmax(not N_child), B = F_c(child) | rmax(not W_child).
@@ -610,24 +650,331 @@ __device__ __forceinline__ void sweep_tile(const SweepJob &J, const DevTables &T
         const Set256 Fo = five_lut(lut + 192 * (2 - c), make_uint4(s0.y, s1.y, s2.y, s3.y));
         Set256 W, N;
         combine(Fc, Fo, Wnt, Nnt, W, N);
+        store_parent<D>(J, L.loff[v], W, N, iD, g0, nparents, l4, q);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Tiles of sibling lines
+//
+// A second staged quadrant F whose patterns have one empty cell: such a
+// pattern has one child, and the patterns in the order of their children form
+// families with a common child.  The tile's lines along D are the patterns of a
+// run of whole families along F (T.run_order), the other two indices fixed:
+// the children along F of all its parents are then the entries of a few
+// child lines along D, which no other tile needs.  They are staged as records
+// like those along D, so that a section with empty cells in two quadrants
+// needs no prepared-term tables in HBM (written by a pass of 1100 VALU
+// instructions per child entry and read, 64 scattered bytes, by each parent).
+// A child line is a line of its own for the five-sets (quadrant F holds the
+// child's pattern), of the mover's colour only.
+// ---------------------------------------------------------------------------
+
+struct RunLds {
+    ChildPosRec *cpos;  // [cmD]
+    uint4 *loff;        // [G] offset coefficients of the parent lines, [G] of the child lines along D, [F] along F
+    uint2 *sel;         // [4][sel_stride(mD)]
+    uint2 *lut;         // [G][kLutStride], then [F][kKidLut]
+    uint2 *O;           // [2 G + F][kOSlots]
+    uint32_t *rec;      // along D: [G][cmD][kRecWords]
+    uint32_t *krec;     // along F: [F][mD][kRecWords]
+    LineMasks *lmq;     // [2 G + F][4]
+    uint32_t *line;     // [G]: pattern index along F | number of its child line << 12 | turns << 16
+    uint32_t *kid;      // [F]: pattern index of the child, then the number of child lines
+    PosChild *pch;      // [mD]
+};
+
+constexpr int kKidLut = 193;  // uint2 per child line; an odd stride staggers the banks
+
+__host__ __device__ __forceinline__ int run_lds(int G, int F, int mD, int cmD, RunLds *L, char *base)
+{
+    int off = 0;
+    auto take = [&](int bytes) {
+        const int at = off;
+        off += bytes;
+        return base + at;
+    };
+    char *p = take(cmD * (int)sizeof(ChildPosRec));
+    if (L) L->cpos = (ChildPosRec *)p;
+    p = take((2 * G + F) * 16);
+    if (L) L->loff = (uint4 *)p;
+    p = take(4 * sel_stride(mD) * 8);
+    if (L) L->sel = (uint2 *)p;
+    p = take((G * kLutStride + F * kKidLut) * 8);
+    if (L) L->lut = (uint2 *)p;
+    p = take((2 * G + F) * kOSlots * 8);
+    if (L) L->O = (uint2 *)p;
+    p = take(G * cmD * kRecWords * 4);
+    if (L) L->rec = (uint32_t *)p;
+    p = take(F * mD * kRecWords * 4);
+    if (L) L->krec = (uint32_t *)p;
+    p = take((2 * G + F) * 4 * (int)sizeof(LineMasks));
+    if (L) L->lmq = (LineMasks *)p;
+    p = take(G * 4);
+    if (L) L->line = (uint32_t *)p;
+    p = take((F + 1) * 4);
+    if (L) L->kid = (uint32_t *)p;
+    p = take(mD * (int)sizeof(PosChild));
+    if (L) L->pch = (PosChild *)p;
+    return off;
+}
+
+int sweep_run_lds_bytes(int G, int F, int mD, int cmD) { return run_lds(G, F, mD, cmD, nullptr, nullptr); }
+
+// v[j] for a j that is uniform but not constant (selected: indexing the
+// kernel's own copy of a job would put it into scratch).
+template <class X>
+__device__ __forceinline__ X pick4(const X (&v)[4], int j)
+{
+    return j == 0 ? v[0] : j == 1 ? v[1] : j == 2 ? v[2] : v[3];
+}
+
+// OR into A and B the record at p turned k times along dimension IP (< 3) of
+// the internal layout (shift_dim with a turn count of its own per lane).
+template <int IP>
+__device__ __forceinline__ void or_turned(Set256 &A, Set256 &B, const uint32_t *p, int k)
+{
+    uint32_t w[16];
+#pragma unroll
+    for (int i = 0; i < 16; i += 2) {
+        const uint2 v = *(const uint2 *)(p + i);
+        w[i] = v.x;
+        w[i + 1] = v.y;
+    }
+    if constexpr (IP == 2) {
+        const bool two = (k & 2) != 0, one = (k & 1) != 0;
+#pragma unroll
+        for (int i = 0; i < 16; i += 2) {
+            const uint32_t x = two ? w[i + 1] : w[i], y = two ? w[i] : w[i + 1];
+            const uint32_t xy = (x << 16) | (y >> 16), yx = (y << 16) | (x >> 16);
+            w[i] = one ? xy : x;
+            w[i + 1] = one ? yx : y;
+        }
+    } else {
+        const int up = IP == 0 ? k : 4 * k, down = (IP == 0 ? 4 : 16) - up;
+        const uint32_t keep = IP == 0 ? 0x11111111u * ((0xfu << up) & 0xfu) : 0x00010001u * ((0xffffu << up) & 0xffffu);
+#pragma unroll
+        for (int i = 0; i < 16; i++) w[i] = bfi(keep, w[i] << up, w[i] >> down);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+        A.w[i] |= w[i];
+        B.w[i] |= w[8 + i];
+    }
+}
+
+template <int D>
+__device__ __forceinline__ void sweep_run_tile(const SweepJob &J, const DevTables &T, uint32_t tile, void *lds_base)
+{
+    const int F = J.fam, c = J.mover, mD = J.m[D], cmD = J.cm[D];
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, nwaves = (int)blockDim.x >> 6;
+    // tile = (run * m_O1 + i_O1) * m_O2 + i_O2
+    const uint32_t mo1 = (uint32_t)(J.o1 == 0 ? J.m[0] : J.o1 == 1 ? J.m[1] : J.m[2]);
+    const uint32_t mo2 = (uint32_t)(J.o2 == 1 ? J.m[1] : J.o2 == 2 ? J.m[2] : J.m[3]);
+    const uint32_t rest = tile / mo2, i_o2 = tile - rest * mo2;
+    const uint32_t run = rest / mo1, i_o1 = rest - run * mo1;
+    const int lo = T.run_start[J.frun + run], nl = T.run_start[J.frun + run + 1] - lo;
+    const RunLds L = [&] {
+        RunLds l;
+        run_lds(J.flines, J.fkids, mD, cmD, &l, (char *)lds_base);
+        return l;
+    }();
+    Idx4 base;
+#pragma unroll
+    for (int j = 0; j < 4; j++) base.v[j] = j == J.o1 ? (int)i_o1 : j == J.o2 ? (int)i_o2 : 0;
+    auto with = [&](int iD, int iF) {
+        Idx4 x = base;
+#pragma unroll
+        for (int j = 0; j < 4; j++) x.v[j] = j == D ? iD : j == F ? iF : base.v[j];
+        return x;
+    };
+    const int qbF = pick4(J.qb, F), cqbF = pick4(J.cqb, F);
+
+    // Phase 0.  The first wave: the run's patterns, their children and the
+    // LineMasks of all lines.  The others: the positions along D.
+    if (wave == 0) {
+        uint32_t rec = 0;
+        if (lane < nl) rec = T.run_order[(c - 1) * kPatterns + qbF + lo + lane];
+        const uint32_t p = rec & 0xfffu, kid = (rec >> 12) & 0xfffu;
+        const uint32_t before = (uint32_t)__shfl_up((int)kid, 1, 64);
+        const bool fresh = lane < nl && (lane == 0 || before != kid);
+        const uint64_t all = __ballot(fresh);
+        const int number = __popcll(all & ((2ull << lane) - 1ull)) - 1, nk = __popcll(all);
+        int cs[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) cs[i] = i == D ? J.cm[i] : J.m[i];
+        if (lane < nl) {
+            L.line[lane] = p | ((uint32_t)number << 12) | ((rec >> 24) << 16);
+            L.loff[lane] = line_offset_coeffs<D>(J.m, with(0, (int)p).v);
+            L.loff[J.flines + lane] = line_offset_coeffs<D>(cs, with(0, (int)p).v);
+        }
+        if (fresh) {
+            L.kid[number] = kid;
+#pragma unroll
+            for (int i = 0; i < 4; i++) cs[i] = i == F ? J.cm[i] : J.m[i];
+            L.loff[2 * J.flines + number] = line_offset_coeffs<D>(cs, with(0, (int)kid).v);
+        }
+        if (lane == 0) L.kid[J.fkids] = (uint32_t)nk;
+        __builtin_amdgcn_wave_barrier();
+        // set vx: line vx >> 1, colour (vx & 1) + 1; from 2 nl: child line vx - 2 nl, the mover's colour
+        for (int it = lane; it < 4 * (2 * nl + nk); it += 64) {
+            const int vx = it >> 2, j = it & 3;
+            const bool kid = vx >= 2 * nl;
+            const int x = kid ? c - 1 : vx & 1;
+            int at = get4(base, j) + pick4(J.qb, j);
+            if (j == F) at = kid ? cqbF + (int)L.kid[vx - 2 * nl] : qbF + (int)(L.line[vx >> 1] & 0xfffu);
+            const LineMasks lm = T.pat_lm[((j * kPatterns + at) << 1) + x];
+            const bool keep = j != D;
+            L.lmq[it] = LineMasks{keep ? lm.a : 0u, keep ? lm.b : 0u, keep ? lm.c : 0u};
+            if (j == 0) L.O[kOSlots * vx + 18] = make_uint2(0, 0);  // U, ORed in line_tables
+        }
+    }
+    const int sst = sel_stride(mD);
+    if (wave > 0 || nwaves == 1) {
+        const int skip = nwaves == 1 ? 0 : 64;
+        for (int it = tid - skip; it < mD + cmD; it += (int)blockDim.x - skip) {
+            const int p = it < mD ? J.qb[D] + it : J.cqb[D] + (it - mD);
+            const uint4 *ps = T.pat_sel + 2 * (((D * kPatterns + p) << 1) + c - 1);
+            const uint4 sc = ps[0], so = ps[1];
+            if (it < mD) {
+                L.sel[it] = make_uint2(sc.x, so.x);
+                L.sel[sst + it] = make_uint2(sc.y, so.y);
+                L.sel[2 * sst + it] = make_uint2(sc.z, so.z);
+                L.sel[3 * sst + it] = make_uint2(sc.w, so.w);
+                L.pch[it] = T.pat_child[(p << 1) + c - 1];
+            } else {
+                L.cpos[it - mD].sel_c = sc;
+                L.cpos[it - mD].sel_o = so;
+            }
+        }
+    }
+    __syncthreads();
+
+    // Child items, 64 to a wave at a time: nl child lines of cmD entries along
+    // D, then nk of mD entries along F.  The first one's entry is on its way
+    // while the line tables are built.
+    const int nk = (int)L.kid[J.fkids], nD = nl * cmD, nF = nk * mD;
+    const int chunksD = (nD + 63) >> 6, chunks = chunksD + ((nF + 63) >> 6);
+    const uint32_t magicD = cmD > 1 ? 0xffffffffu / (uint32_t)cmD + 1u : 0u, magicF = mD > 1 ? 0xffffffffu / (uint32_t)mD + 1u : 0u;
+    int line = 0, at = 0;  // line (or child line) and position along D of this lane's item
+    auto child_item = [&](int ch) {
+        const bool kid = ch >= chunksD;
+        const int r = min(64 * (kid ? ch - chunksD : ch) + lane, (kid ? nF : nD) - 1), len = kid ? mD : cmD;
+        const uint32_t magic = kid ? magicF : magicD;
+        line = len > 1 ? (int)__umulhi((uint32_t)r, magic) : r;
+        at = r - line * len;
+        return kid;
+    };
+    auto child_entry = [&](bool kid) -> const uint4 * {
+        const uint4 lc = L.loff[J.flines + (kid ? J.flines : 0) + line];
+        const uint32_t b = (uint32_t)at >> 3, e = min(8u, (uint32_t)(kid ? mD : cmD) - 8u * b);
+        return pick4(J.child, kid ? F : D) + 4 * (size_t)(lc.x + lc.y * b + lc.z * e + __umul24(lc.w, (uint32_t)at & 7u));
+    };
+    uint4 pre[4] = {};
+    if (wave < chunks) {
+        const bool kid = child_item(wave);
+        const uint4 *p = child_entry(kid);
+#pragma unroll
+        for (int i = 0; i < 4; i++) pre[i] = p[i];
+    }
+    {
+        const int sets = 2 * nl + nk;
+        const uint32_t refs0 = tid < sets * 33 ? partial_refs<D>(T, tid) : 0u;
+        line_tables<D>(T, L.lmq, L.O, sets, refs0, [&](int vx) {
+            return vx < 2 * nl ? L.lut + kLutStride * (vx >> 1) + 192 * (vx & 1)
+                               : L.lut + kLutStride * J.flines + kKidLut * (vx - 2 * nl);
+        });
+    }
+
+    // Phase 1: child records
+    for (int ch = wave; ch < chunks; ch += nwaves) {
+        const bool kid = child_item(ch);
+        if (ch != wave) {
+            const uint4 *p = child_entry(kid);
+#pragma unroll
+            for (int i = 0; i < 4; i++) pre[i] = p[i];
+        }
+        Set256 W = set_from(pre), N = set_from(pre + 2);
         swap_with3<D>(W);
         swap_with3<D>(N);
-        uint4 r[4] = {make_uint4(W.w[0], W.w[1], W.w[2], W.w[3]), make_uint4(W.w[4], W.w[5], W.w[6], W.w[7]),
-                      make_uint4(N.w[0], N.w[1], N.w[2], N.w[3]), make_uint4(N.w[4], N.w[5], N.w[6], N.w[7])};
-        quad_transpose(r, l4);
-        const uint4 lc = L.loff[v];
-        const uint32_t bD = (uint32_t)iD >> 3;
-        const uint32_t sD = min(8u, (uint32_t)mD - 8u * bD), rD = (uint32_t)iD & 7u;
-        // for D = 3 every coefficient but c0 is below 2^13 (products of block
-        // extents), so 24-bit multiplies are exact
-        const uint32_t off = D == 3 ? lc.x + __umul24(lc.y, bD) + __umul24(lc.z, sD) + rD
-                                    : lc.x + lc.y * bD + lc.z * sD + lc.w * rD;
-        const uint32_t offs[4] = {quad_perm<0x00>(off), quad_perm<0x55>(off), quad_perm<0xAA>(off),
-                                  quad_perm<0xFF>(off)};
+        uint4 sel;
+        const uint2 *lut;
+        if (kid) {
+            sel = make_uint4(L.sel[at].x, L.sel[sst + at].x, L.sel[2 * sst + at].x, L.sel[3 * sst + at].x);
+            lut = L.lut + kLutStride * J.flines + kKidLut * line;
+        } else {
+            sel = L.cpos[at].sel_c;
+            lut = L.lut + kLutStride * line + 192 * (c - 1);
+        }
+        const Set256 Fc = five_lut(lut, sel);
+        Set256 A, B;
+        child_terms(Fc, W, N, A, B);
+        if (64 * (kid ? ch - chunksD : ch) + lane < (kid ? nF : nD)) {
+            uint32_t *r = kid ? L.krec + kRecWords * (line * mD + at) : L.rec + kRecWords * (line * cmD + at);
 #pragma unroll
-        for (int p = 0; p < 4; p++)
-            if (g0 + 16 * p + q < nparents) store_stream(J.out + 4 * offs[p] + l4, r[p]);
+            for (int i = 0; i < 8; i += 2) {
+                *(uint2 *)(r + i) = make_uint2(A.w[i], A.w[i + 1]);
+                *(uint2 *)(r + 8 + i) = make_uint2(B.w[i], B.w[i + 1]);
+            }
+        }
     }
+    __syncthreads();
+
+    // Phase 2: parents, 64 consecutive ones along D to a wave (see sweep_tile)
+    const int l4 = lane & 3, q = lane >> 2, n = nl * mD;
+    const int ip = F == 3 ? D : F;  // F's place in the internal layout (D is at 3)
+    for (int g0 = 64 * wave; g0 < n; g0 += 64 * nwaves) {
+        const int P = min(g0 + 16 * l4 + q, n - 1);  // a spare lane repeats the last parent
+        const int v = mD > 1 ? (int)__umulhi((uint32_t)P, magicF) : P, iD = P - v * mD;
+        const uint32_t info = L.line[v];
+        Set256 Wnt, Nnt;
+        {
+            const PosChild &pr = L.pch[iD];
+            const uint32_t *own = L.rec + kRecWords * (v * cmD);
+            const uint32_t c0 = pr.child[0];
+            const uint32_t *r0 = own + kRecWords * (c0 & 0xfff);
+            Wnt = load_rotated(r0, c0 >> 12);
+            Nnt = load_rotated(r0 + 8, c0 >> 12);
+            for (int e = 1; e < J.nchd; e++) {
+                const uint32_t cc = pr.child[e];
+                const uint32_t *r = own + kRecWords * (cc & 0xfff);
+                or_rotated(Wnt, r, cc >> 12);
+                or_rotated(Nnt, r + 8, cc >> 12);
+            }
+        }
+        {
+            const uint32_t *r = L.krec + kRecWords * ((int)((info >> 12) & 15u) * mD + iD);
+            const int k = (int)(info >> 16);
+            if (ip == 0) or_turned<0>(Wnt, Nnt, r, k);
+            else if (ip == 1) or_turned<1>(Wnt, Nnt, r, k);
+            else or_turned<2>(Wnt, Nnt, r, k);
+        }
+        // children along the remaining dimensions with empty cells
+        const int left = J.emask & ~(1 << D) & ~(1 << F);
+        if (left) {
+            const Idx4 idx = with(iD, (int)(info & 0xfffu));
+            if (D != 0 && (left & 1)) direct_children<D, 0>(J, T, idx, Wnt, Nnt);
+            if (D != 1 && (left & 2)) direct_children<D, 1>(J, T, idx, Wnt, Nnt);
+            if (D != 2 && (left & 4)) direct_children<D, 2>(J, T, idx, Wnt, Nnt);
+            if (D != 3 && (left & 8)) direct_children<D, 3>(J, T, idx, Wnt, Nnt);
+        }
+        const uint2 *lut = L.lut + kLutStride * v;
+        const uint2 s0 = L.sel[iD], s1 = L.sel[sst + iD], s2 = L.sel[2 * sst + iD], s3 = L.sel[3 * sst + iD];
+        const Set256 Fc = five_lut(lut + 192 * (c - 1), make_uint4(s0.x, s1.x, s2.x, s3.x));
+        const Set256 Fo = five_lut(lut + 192 * (2 - c), make_uint4(s0.y, s1.y, s2.y, s3.y));
+        Set256 W, N;
+        combine(Fc, Fo, Wnt, Nnt, W, N);
+        store_parent<D>(J, L.loff[v], W, N, iD, g0, n, l4, q);
+    }
+}
+
+// Workgroups reach the 8 XCDs in turn: the b-th of n takes this tile, so that
+// each XCD works through a contiguous range of tiles, and the two entries of a
+// 128-byte line that neighbouring tiles touch meet in one L2.
+__device__ __forceinline__ uint32_t xcd_range(uint32_t b, uint32_t n)
+{
+    const uint32_t per = n >> 3, rem = n & 7u, x = b & 7u;
+    return x * per + min(x, rem) + (b >> 3);
 }
 
 // 512 threads: at most 64 VGPRs (8 waves per SIMD, no scratch), so that four
@@ -638,13 +985,7 @@ template <int D, int NT, bool SYMC = false>
 __global__ void __launch_bounds__(NT, NT == 512 ? (SYMC ? 5 : 8) : 1) sweep_kernel(SweepJob J, DevTables T)
 {
     extern __shared__ uint4 lds[];
-    uint32_t tile = blockIdx.x;
-    if (J.order == 1) {
-        // workgroups go to the 8 XCDs in turn: XCD x = b % 8 takes the x-th
-        // contiguous range of tiles (ranges differ in size by at most one)
-        const uint32_t n = (uint32_t)J.ntiles, per = n >> 3, rem = n & 7u, x = tile & 7u;
-        tile = x * per + min(x, rem) + (tile >> 3);
-    }
+    const uint32_t tile = J.order == 1 ? xcd_range(blockIdx.x, (uint32_t)J.ntiles) : blockIdx.x;
     sweep_tile<D, SYMC>(J, T, tile, (void *)lds);
 }
 
@@ -652,8 +993,10 @@ __global__ void __launch_bounds__(NT, NT == 512 ? (SYMC ? 5 : 8) : 1) sweep_kern
 // the job whose tiles start at tile_start[j] <= b.  The hardware dispatcher
 // hands out the tiles (measured faster than a persistent grid pulling tiles
 // from a device counter: no queue atomic, no job table re-read per tile, and
-// a new workgroup starts as soon as one ends).  SYMS: some staged children
-// are held as their representatives (sweep_tile<D, true> for those jobs).
+// a new workgroup starts as soon as one ends; contiguous ranges per XCD, which
+// help a single section, lose 15 % here, as the ranges hold different jobs).
+// SYMS: some staged children are held as their representatives
+// (sweep_tile<D, true> for those jobs).
 template <bool SYMS>
 __device__ __forceinline__ void sweep_batch_tile(const SweepJob *jobs, const long long *tile_start, int njobs,
                                                  long long total, const DevTables &T)
@@ -730,6 +1073,12 @@ hipError_t launch_sweep(const SweepJob &job, const DevTables &T, hipStream_t s)
 {
     if (job.ntiles == 0) return hipSuccess;
     const dim3 grid((unsigned)job.ntiles), block(job.threads);
+    if (job.threads != 256 && job.threads != 512) return hipErrorInvalidValue;
+    if (job.fam >= 0) {
+        if (job.threads == 512) hipLaunchKernelGGL(sweep_run_kernel<512>, grid, block, job.lds_bytes, s, job, T);
+        else hipLaunchKernelGGL(sweep_run_kernel<256>, grid, block, job.lds_bytes, s, job, T);
+        return hipGetLastError();
+    }
     const bool symc = job.csym[job.d & 3] != 0 && ((job.emask >> job.d) & 1) && !((job.odmask >> job.d) & 1);
     if (symc) {
         // the staged child read through a board symmetry

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <numeric>
 
 namespace pg {
 
@@ -271,6 +272,49 @@ static void build_pattern_lookups(HostTables &t)
     }
 }
 
+static void build_runs(HostTables &t)
+{
+    t.run_order.assign(2 * kPatterns, 0);
+    int classes = 0;
+    for (int b = 0; b <= 9; b++)
+        for (int w = 0; w <= 9; w++) t.class_number[b][w] = b + w <= 9 ? classes++ : -1;
+    for (int cap = 0; cap < kRunCaps; cap++)
+        for (int x = 0; x < 2; x++) t.runs[cap][x].assign(classes, RunClass{0, 0, 0, 0});
+    for (int x = 1; x <= 2; x++)
+        for (int b = 0; b <= 8; b++) {
+            const int w = 8 - b, first = t.class_start[b][w], n = t.class_size[b][w];
+            auto child = [&](int i) { return t.pat_child[(first + i) * 2 + x - 1].child[0] & 0xfff; };
+            std::vector<int> order(n);
+            std::iota(order.begin(), order.end(), 0);
+            std::stable_sort(order.begin(), order.end(), [&](int p, int q) { return child(p) < child(q); });
+            for (int i = 0; i < n; i++) {
+                const uint32_t c = t.pat_child[(first + order[i]) * 2 + x - 1].child[0];
+                t.run_order[(x - 1) * kPatterns + first + i] = (uint32_t)order[i] | (c & 0xfffu) << 12 | (c >> 12) << 24;
+            }
+            for (int cap = 0; cap < kRunCaps; cap++) {
+                RunClass &R = t.runs[cap][x - 1][t.class_number[b][w]];
+                R.start = (int)t.run_start.size();
+                int at = 0;
+                while (at < n) {
+                    t.run_start.push_back((uint16_t)at);
+                    int end = at, children = 0;
+                    while (end < n && children < kRunCap[cap].kids) {
+                        int f = end + 1;
+                        while (f < n && child(order[f]) == child(order[end])) f++;
+                        if (f - at > kRunCap[cap].patterns && end > at) break;
+                        end = std::min(f, at + kRunCap[cap].patterns);
+                        children++;
+                    }
+                    R.count++;
+                    R.max_patterns = std::max(R.max_patterns, end - at);
+                    R.max_children = std::max(R.max_children, children);
+                    at = end;
+                }
+                t.run_start.push_back((uint16_t)n);
+            }
+        }
+}
+
 static void build(HostTables &t)
 {
     const int NC = 19683;
@@ -317,6 +361,7 @@ static void build(HostTables &t)
     build_line_masks(t);
     build_line_structure(t);
     build_pattern_lookups(t);
+    build_runs(t);
 }
 
 const HostTables &host_tables()

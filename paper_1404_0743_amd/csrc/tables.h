@@ -26,6 +26,21 @@ struct alignas(4) PosChild {
     uint16_t nchild, child[9];
 };
 
+// The patterns of a class with one empty cell when one side moves, in the
+// order of their one child and cut into runs of at most patterns[cap]
+// patterns of at most kids[cap] children: whole families of siblings unless
+// a family is longer.  Families have as many patterns as the child has stones
+// of the mover, mostly 2 to 7.
+constexpr int kRunCaps = 4;
+struct RunCap {
+    int patterns, kids;
+};
+constexpr RunCap kRunCap[kRunCaps] = {{10, 3}, {8, 2}, {7, 1}, {5, 1}};
+struct RunClass {
+    int start, count;                 // run_start[start .. start + count]
+    int max_patterns, max_children;   // the most of any run
+};
+
 struct HostTables {
     int class_start[10][10];
     int class_size[10][10];
@@ -79,6 +94,15 @@ struct HostTables {
     std::vector<LineMasks> pat_lm;     // [4 * kPatterns * 2]
     std::vector<uint32_t> pat_sel;     // [4 * kPatterns * 2 * 2 * 4]
     std::vector<PosChild> pat_child;   // [kPatterns * 2]
+
+    // Runs (RunClass): run_order[(c - 1) * kPatterns + class start + i] holds
+    // the class index of the i-th pattern by child when c moves, | its child's
+    // class index << 12 | the turns to it << 24; run_start the positions i where
+    // the runs of a class start, and its end; runs[cap][c - 1] by class_number.
+    int class_number[10][10];
+    std::vector<uint32_t> run_order;   // [2 * kPatterns]
+    std::vector<uint16_t> run_start;
+    std::vector<RunClass> runs[kRunCaps][2];
 };
 
 // Built once on first use (thread-safe).

@@ -25,7 +25,7 @@ TileShape tuned_tile_shape(const SweepJob &J)
 {
     std::lock_guard<std::mutex> lock(g_tune_mutex);
     auto it = g_tile_cache.find(tile_key(J));
-    return it == g_tile_cache.end() ? TileShape{0, 0, 0} : it->second;
+    return it == g_tile_cache.end() ? TileShape{0, 0, 0, false} : it->second;
 }
 
 void remember_tile_shape(const SweepJob &J, TileShape t)
@@ -40,7 +40,7 @@ int run_job(SweepJob &J, const DevTables &T, hipStream_t st)
     void *prep[4] = {nullptr, nullptr, nullptr, nullptr};
     hipError_t e = hipSuccess;
     for (int j = 0; j < 4 && e == hipSuccess; j++) {
-        if (j == J.d || !((J.emask >> j) & 1)) continue;
+        if (j == J.d || j == J.fam || !((J.emask >> j) & 1)) continue;
         e = hipMallocAsync(&prep[j], prep_bytes(J, j), st);
         if (e != hipSuccess) break;
         J.prep[j] = J.prep_out[j] = (uint4 *)prep[j];
@@ -72,32 +72,42 @@ extern "C" int pentago_autotune_section(pentago_section s, const pentago_superin
     hipEvent_t a, b;
     if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess)
         return fail(PENTAGO_EDEVICE, "hipEventCreate");
-    TileShape best_shape{0, 0, 0};
+    TileShape best_shape{0, 0, 0, false};
     float best = 1e30f;
-    const int cmd = (J0.emask >> J0.d) & 1 ? J0.cm[J0.d] : 0;
+    auto time = [&](SweepJob &J) {
+        rc = run_job(J, T, st);  // warm-up
+        float t = 1e30f;
+        for (int rep = 0; rep < 3 && rc == 0; rep++) {
+            (void)hipEventRecord(a, st);
+            rc = run_job(J, T, st);
+            (void)hipEventRecord(b, st);
+            if (hipEventSynchronize(b) != hipSuccess) rc = fail(PENTAGO_EDEVICE, "hipEventSynchronize");
+            float ms = 0;
+            (void)hipEventElapsedTime(&ms, a, b);
+            t = std::min(t, ms);
+        }
+        return t;
+    };
     for (int order = 0; order < 2 && rc == 0; order++) {
         for (int nt = 256; nt <= 512 && rc == 0; nt *= 2) {
             for (int G = 1; G <= 8 && rc == 0; G++) {
-                if (sweep_lds_bytes(G, J0.m[J0.d], cmd) > 65536) break;
                 SweepJob J;
                 rc = make_job(s, child, out, &J, -1, G, nt, order);
-                if (rc) break;
-                rc = run_job(J, T, st);  // warm-up
-                float t = 1e30f;
-                for (int rep = 0; rep < 3 && rc == 0; rep++) {
-                    (void)hipEventRecord(a, st);
-                    rc = run_job(J, T, st);
-                    (void)hipEventRecord(b, st);
-                    if (hipEventSynchronize(b) != hipSuccess) rc = fail(PENTAGO_EDEVICE, "hipEventSynchronize");
-                    float ms = 0;
-                    (void)hipEventElapsedTime(&ms, a, b);
-                    t = std::min(t, ms);
-                }
+                if (rc || J.lds_bytes > 65536) break;
+                const float t = time(J);
                 if (rc == 0 && t < best) {
                     best = t;
-                    best_shape = TileShape{G, nt, order};
+                    best_shape = TileShape{G, nt, order, false};
                 }
             }
+        }
+    }
+    SweepJob Jr = J0;
+    if (rc == 0 && make_run(s, &Jr, kRunLdsCap)) {
+        const float t = time(Jr);
+        if (rc == 0 && t < best) {
+            best = t;
+            best_shape.runs = true;
         }
     }
     (void)hipEventDestroy(a);
@@ -106,8 +116,11 @@ extern "C" int pentago_autotune_section(pentago_section s, const pentago_superin
     remember_tile_shape(J0, best_shape);
     // leave out holding the result of the chosen shape
     SweepJob J;
-    rc = make_job(s, child, out, &J, -1, best_shape.lines, best_shape.threads, best_shape.order);
-    if (rc == 0) rc = run_job(J, T, st);
+    rc = make_job(s, child, out, &J, -1, 0);
+    if (rc == 0) {
+        take_siblings(s, &J);
+        rc = run_job(J, T, st);
+    }
     if (shape) *shape = pentago_tile_shape{best_shape.lines, best_shape.threads, best_shape.order};
     if (best_ms) *best_ms = best;
     return rc;

@@ -216,3 +216,64 @@ def test_out_overlapping_a_child_is_rejected(P):
     torch.cuda.synchronize()
     want = O.section_solve(counts, [None] * 4)
     assert np.array_equal(from_dev(buf[nc:nc + n]), want)
+
+
+def _placed(d, f, cd, cf, rest):
+    """Classes cd at quadrant d, cf at quadrant f, rest at the other two."""
+    counts = [None] * 4
+    counts[d], counts[f] = cd, cf
+    o = [j for j in range(4) if counts[j] is None]
+    counts[o[0]], counts[o[1]] = rest
+    return tuple(counts)
+
+
+# small sections in tiles of sibling lines: lines along each quadrant with the
+# siblings along each other one; the longest lines (the smaller runs); the
+# size at which tiles of lines take over (0.76 and 1.33 million entries); one
+# empty cell in both quadrants; empty cells in three
+SIBLINGS = ([_placed(d, f, (1, 6), (7, 1), ((7, 2), (2, 7))) for d in range(4) for f in range(4) if d != f] +
+            [((4, 3), (4, 4), (9, 0), (0, 9)),
+             ((9, 0), (4, 4), (0, 9), (3, 3)),
+             ((7, 1), (4, 3), (0, 9), (6, 3)),
+             ((2, 5), (7, 1), (2, 7), (6, 3)),
+             ((1, 6), (7, 1), (5, 4), (4, 5)),
+             ((6, 2), (7, 1), (2, 7), (2, 7)),
+             ((4, 4), (4, 5), (8, 0), (1, 8)),
+             ((6, 2), (1, 7), (2, 7), (8, 0))])
+
+
+@pytest.mark.parametrize("counts", SIBLINGS, ids=str)
+def test_sibling_tiles(P, counts):
+    """The sweep as the library lays it out, against tiles of lines of two
+    shapes on every entry and against O4 on sampled ones; the sweep over the
+    children's representatives and the autotuned sweep give the same table."""
+    log("siblings", counts, O.section_entries(counts))
+    cache = {}
+    got = gpu_chain(P, counts, cache)
+    children = [cache[O.child_counts(counts, j)] if sum(counts[j]) < 9 else None for j in range(4)]
+    for shape in ((1, 512, 1), (1, 256, 0)):
+        lines = torch.zeros_like(got)
+        P.pentago_solve_section_shape(counts, children, lines, *shape)
+        assert torch.equal(got, lines), shape
+    rng = np.random.default_rng(5)
+    n = len(got)
+    pick = np.unique(np.concatenate([[0, n - 1], rng.integers(0, n, 100)]))
+    idx = O.section_all_indices(counts)[pick]
+    want = O.section_solve(counts, [None if c is None else from_dev(c) for c in children], idx)
+    assert np.array_equal(from_dev(got)[pick], want)
+    reps = [None] * 4
+    for j in range(4):
+        if sum(counts[j]) < 9:
+            child = O.child_counts(counts, j)
+            rep, sym = P.pentago_section_standardize(child)
+            back = next(g for g in range(8) if P.pentago_section_image(child, g) == rep)
+            reps[j] = torch.empty((O.section_entries(rep), 8), dtype=torch.int64, device="cuda")
+            P.pentago_section_transform(child, children[j], back, reps[j])
+    d4 = torch.zeros_like(got)
+    P.pentago_solve_section_d4(counts, reps, d4)
+    assert torch.equal(got, d4)
+    tuned = torch.zeros_like(got)
+    P.pentago_autotune_section(counts, children, tuned)
+    again = torch.zeros_like(got)
+    P.pentago_solve_section(counts, children, again)
+    assert torch.equal(got, tuned) and torch.equal(got, again)
