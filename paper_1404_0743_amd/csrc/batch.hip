@@ -22,7 +22,7 @@ struct pentago_sweep_plan {
     int lds_bytes = 0;
     int threads = 512;  // per tile workgroup
     // jobs [0, nbig) have tiles above the LDS cap even with one line;
-    // they take a second launch, beside the first on a side stream
+    // they take a launch of their own, before the others'
     int nbig = 0;
     long long tiles_big = 0;
     int lds_big = 0;
@@ -83,6 +83,10 @@ static int plan_build(const pentago_section_job *jobs, size_t n, hipStream_t str
     for (size_t i = 0; i < n; i++) {
         if (section_stones(jobs[i].section) != stones)
             return fail(PENTAGO_EINVAL, "jobs of one call must share the stone count");
+        // (tiles of sibling lines, faster for single sections, lose here: the
+        // launch's one LDS size and workgroup size suit few of a layer's
+        // sections, and the prep launch they save is shared by all; layer 33
+        // took 0.98 ms with them against 0.58, layer 34 0.47 against 0.40)
         int rc = make_job(jobs[i].section, jobs[i].child, jobs[i].out, &J[i], -1, 0);
         if (rc) return rc;
         // in a batch, stage the quadrant with the longest lines (the most
@@ -218,47 +222,19 @@ static int plan_build(const pentago_section_job *jobs, size_t n, hipStream_t str
     return 0;
 }
 
-// The side stream of the current device (default priority), for the
-// launch of the large-LDS tiles beside the others.
-static hipStream_t side_stream()
-{
-    static std::mutex mu;
-    static hipStream_t st[64];
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    if (dev < 0 || dev >= 64) return nullptr;
-    std::lock_guard<std::mutex> lock(mu);
-    if (!st[dev] && hipStreamCreateWithFlags(&st[dev], hipStreamNonBlocking) != hipSuccess) st[dev] = nullptr;
-    return st[dev];
-}
-
 static int plan_enqueue(pentago_sweep_plan *P, hipStream_t st)
 {
     hipError_t e = launch_prep_batch(P->d_jobs, P->d_unit, P->d_chunk_start, P->nunits,
                                      P->total_chunks, P->T, st);
-    const bool both = P->tiles_big > 0 && P->total_tiles > 0;
-    hipStream_t side = both ? side_stream() : nullptr;
-    if (both && !side) return fail(PENTAGO_EDEVICE, "side stream");
-    hipEvent_t fork = nullptr, join = nullptr;
-    if (e == hipSuccess && both) {
-        e = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&join, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventRecord(fork, st);
-        if (e == hipSuccess) e = hipStreamWaitEvent(side, fork, 0);
-    }
-    // the large-LDS tiles on the caller's stream, the others beside them
+    // the large-LDS tiles, then the others on the same stream (beside them on
+    // a second stream the 64-section layers took 2.8 % more at 34 stones, 407 us
+    // against 396, and 3.4 % more at 33: the two LDS sizes crowd each other out)
     if (e == hipSuccess && P->tiles_big > 0)
         e = launch_sweep_batch(P->d_jobs, P->d_tile_start, P->nbig, P->tiles_big, P->lds_big, P->threads, P->sym,
                                P->T, st);
     if (e == hipSuccess && P->total_tiles > 0)
         e = launch_sweep_batch(P->d_jobs + P->nbig, P->d_tile_start + P->nbig, P->njobs - P->nbig,
-                               P->total_tiles, P->lds_bytes, P->threads, P->sym, P->T, both ? side : st);
-    if (e == hipSuccess && both) {
-        e = hipEventRecord(join, side);
-        if (e == hipSuccess) e = hipStreamWaitEvent(st, join, 0);
-    }
-    if (fork) (void)hipEventDestroy(fork);
-    if (join) (void)hipEventDestroy(join);
+                               P->total_tiles, P->lds_bytes, P->threads, P->sym, P->T, st);
     if (e != hipSuccess) return hip_fail(e, "batched sweep launch");
     return 0;
 }

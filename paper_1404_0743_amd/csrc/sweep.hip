@@ -1033,10 +1033,10 @@ __device__ __forceinline__ void sweep_batch_tile(const SweepJob *jobs, const lon
 }
 
 // NT = 256 or 512 threads per tile (the batch autotuner picks one per
-// layer), at least 6 (5 with the symmetry variants) waves per SIMD: three
-// 512-thread workgroups of tiles up to 52 KiB of LDS per CU, as the tuned
-// single-section sweep, or twice as many 256-thread ones where the tiles
-// are small (short lines leave most of 512 threads idle in every phase)
+// layer), at least 6 waves per SIMD: three 512-thread workgroups of tiles up
+// to 52 KiB of LDS per CU, as the tuned single-section sweep, or twice as many
+// 256-thread ones where the tiles are small (short lines leave most of 512
+// threads idle in every phase)
 template <int NT>
 __global__ void __launch_bounds__(NT, 6)
     sweep_batch_kernel(const SweepJob *jobs, const long long *tile_start, int njobs, long long total, DevTables T)
@@ -1044,13 +1044,38 @@ __global__ void __launch_bounds__(NT, 6)
     sweep_batch_tile<false>(jobs, tile_start, njobs, total, T);
 }
 
-// The same over jobs whose children may be held as their representatives.
+// The same over jobs whose children may be held as their representatives.  512
+// threads: registers for 6 waves per SIMD, 24 bytes of scratch per lane included
+// (125 sections of slice 34 over their representatives at 52 KiB: 8.90 ms with
+// registers for 5, 8.15 ms with 6); 256 threads, whose tiles are smaller and whose
+// workgroups more: for 5 (8.54 ms at 32 KiB, 8.80 ms with 6).
 template <int NT>
-__global__ void __launch_bounds__(NT, 5)
+__global__ void __launch_bounds__(NT, NT == 512 ? 6 : 5)
     sweep_batch_sym_kernel(const SweepJob *jobs, const long long *tile_start, int njobs, long long total,
                            DevTables T)
 {
     sweep_batch_tile<true>(jobs, tile_start, njobs, total, T);
+}
+
+__device__ __forceinline__ void sweep_run_any(const SweepJob &J, const DevTables &T, uint32_t tile)
+{
+    extern __shared__ uint4 lds[];
+    switch (J.d) {
+    case 0: sweep_run_tile<0>(J, T, tile, (void *)lds); break;
+    case 1: sweep_run_tile<1>(J, T, tile, (void *)lds); break;
+    case 2: sweep_run_tile<2>(J, T, tile, (void *)lds); break;
+    default: sweep_run_tile<3>(J, T, tile, (void *)lds); break;
+    }
+}
+
+template <int NT>
+__global__ void __launch_bounds__(NT, 6) sweep_run_kernel(SweepJob J, DevTables T)
+{
+    // the job where it lies, in the kernel arguments: a job passed by value and
+    // indexed by quadrant would be copied to scratch
+    (void)J;
+    const SweepJob &job = *(const SweepJob *)__builtin_amdgcn_kernarg_segment_ptr();
+    sweep_run_any(job, T, xcd_range(blockIdx.x, gridDim.x));
 }
 
 hipError_t launch_prep(const SweepJob &job, int j, const DevTables &T, hipStream_t s)
