@@ -51,42 +51,28 @@ __device__ __forceinline__ const uint4 *child_rep_entry(const SweepJob &J, const
 // shift; the immediate-win set of the placement is the child's own five-set
 // of the parent's colour, shifted the same way).
 //   A = F_c(child) | rmax(not N_child),  B = F_c(child) | rmax(not W_child)
-// JD is the child's dimension (the quadrant that received the stone).
+// JD is the child's dimension (the quadrant that received the stone).  The child
+// has a table: full boards worked out on demand are the staged child of their
+// parent.
 template <int JD>
 __device__ __forceinline__ void child_entry_terms(const SweepJob &J, const DevTables &T,
                                                   const Idx4 &idx, Set256 &A, Set256 &B)
 {
-    const int c = J.mover;
-    unsigned cm_[4], om_[4];
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-        const QInfo q = T.qinfo[(j == JD ? J.cqb[j] : J.qb[j]) + idx.v[j]];
-        cm_[j] = c == 1 ? q.bm : q.wm;
-        om_[j] = c == 1 ? q.wm : q.bm;
-    }
     Set256 W, N;
-    if ((J.odmask >> JD) & 1) {
-        // a full board with the other side to move: value f_o - f_c (Section II)
-        const Set256 Fc = board_five(T, cm_);
-        const Set256 Fo = board_five(T, om_);
-#pragma unroll
-        for (int i = 0; i < 8; i++) {
-            W.w[i] = Fo.w[i] & ~Fc.w[i];
-            N.w[i] = Fo.w[i] | ~Fc.w[i];
-        }
+    if (J.csym[JD]) {
+        int h[4];
+        load_info(child_rep_entry<JD>(J, T, idx.v, h), W, N);
+        sym_apply_rt2(W, N, J.csym[JD], h);
     } else {
-        if (J.csym[JD]) {
-            int h[4];
-            load_info(child_rep_entry<JD>(J, T, idx.v, h), W, N);
-            sym_apply_rt2(W, N, J.csym[JD], h);
-        } else {
-            int cshape[4] = {J.m[0], J.m[1], J.m[2], J.m[3]};
-            cshape[JD] = J.cm[JD];
-            load_info(J.child[JD] + 4 * block_offset(cshape, idx.v), W, N);
-        }
+        int cshape[4] = {J.m[0], J.m[1], J.m[2], J.m[3]};
+        cshape[JD] = J.cm[JD];
+        load_info(J.child[JD] + 4 * block_offset(cshape, idx.v), W, N);
     }
-    const Set256 Fc = board_five(T, cm_);
-    child_terms(Fc, W, N, A, B);
+    LineMasks q[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+        q[j] = T.pat_lm[((j * kPatterns + (j == JD ? J.cqb[j] : J.qb[j]) + idx.v[j]) << 1) + J.mover - 1];
+    child_terms(five_set(q[0], q[1], q[2], q[3]), W, N, A, B);
 }
 
 
@@ -274,17 +260,27 @@ __device__ __forceinline__ void direct_children(const SweepJob &J, const DevTabl
 
 // A/B terms of every entry of the child section along JD (for dimensions
 // that a sweep does not stage in LDS), written in the internal layout of the
-// parent's sweep (dimension J.d exchanged with 3).
+// parent's sweep (dimension J.d exchanged with 3).  Bound by VALU issue,
+// half of it the five-set (540 instructions an entry), ahead of the 128 bytes
+// moved.  33 stones with three empty cells, two prep passes in the sweep's time:
+// 345 us with the indices in 64 bits and the line masks by way of the stone
+// masks, 334 with 32 bits and the masks tabulated by pattern.  (In tiles of 8
+// lines, with the five-sets from chunk tables as in sweep_tile, 343, and the
+// 64-section layers took 4 % more: the set-up of the tables costs what it saves.)
 template <int JD>
-__device__ __forceinline__ void prep_entry(const SweepJob &J, const DevTables &T, long long i)
+__device__ __forceinline__ void prep_entry(const SweepJob &J, const DevTables &T, uint32_t i)
 {
     int cshape[4] = {J.m[0], J.m[1], J.m[2], J.m[3]};
     cshape[JD] = J.cm[JD];
+    // (32 bits: block_offset holds the entries of a table to fewer than 2^32)
     Idx4 idx;
-    long long r = i;
-    idx.v[3] = (int)(r % cshape[3]); r /= cshape[3];
-    idx.v[2] = (int)(r % cshape[2]); r /= cshape[2];
-    idx.v[1] = (int)(r % cshape[1]); r /= cshape[1];
+    uint32_t r = i;
+#pragma unroll
+    for (int k = 3; k > 0; k--) {
+        const uint32_t m = (uint32_t)cshape[k], q = r / m;
+        idx.v[k] = (int)(r - q * m);
+        r = q;
+    }
     idx.v[0] = (int)r;
     Set256 A, B;
     child_entry_terms<JD>(J, T, idx, A, B);
@@ -311,7 +307,7 @@ __global__ void __launch_bounds__(256) prep_kernel(SweepJob J, DevTables T)
     const long long n = prep_count(J, JD);
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (long long)gridDim.x * blockDim.x)
-        prep_entry<JD>(J, T, i);
+        prep_entry<JD>(J, T, (uint32_t)i);
 }
 
 // Prep passes of many jobs in one launch: unit u = (job, dimension), its
@@ -332,10 +328,10 @@ __global__ void __launch_bounds__(256)
         const long long i = (ch - chunk_start[lo]) * 256 + threadIdx.x;
         if (i >= prep_count(J, jd)) continue;
         switch (jd) {
-        case 0: prep_entry<0>(J, T, i); break;
-        case 1: prep_entry<1>(J, T, i); break;
-        case 2: prep_entry<2>(J, T, i); break;
-        default: prep_entry<3>(J, T, i); break;
+        case 0: prep_entry<0>(J, T, (uint32_t)i); break;
+        case 1: prep_entry<1>(J, T, (uint32_t)i); break;
+        case 2: prep_entry<2>(J, T, (uint32_t)i); break;
+        default: prep_entry<3>(J, T, (uint32_t)i); break;
         }
     }
 }
