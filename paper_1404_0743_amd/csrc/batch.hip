@@ -59,12 +59,16 @@ constexpr int kBatchCaps[] = {24576, 32768, 40960, 53248};
 constexpr int kBatchThreadChoices[] = {256, 512};
 
 static std::mutex g_shape_mutex;
-static BatchShape g_shape[37];   // per stone count; cap 0: kBatchDefault
+// Per stone count, jobs over representatives (1) apart from the others (0): their
+// kernel needs more registers, and its best shape is another (slice 34 over
+// representatives: 8.10 ms at the default, 8.55 at the 256 threads and 32 KiB
+// that are best for a plain layer of 34 stones).  cap 0: kBatchDefault
+static BatchShape g_shape[2][37];
 
-static BatchShape batch_shape(int stones)
+static BatchShape batch_shape(int stones, bool reps)
 {
     std::lock_guard<std::mutex> lock(g_shape_mutex);
-    const BatchShape b = stones >= 0 && stones <= 36 ? g_shape[stones] : BatchShape{0, 0};
+    const BatchShape b = stones >= 0 && stones <= 36 ? g_shape[reps][stones] : BatchShape{0, 0};
     return b.cap > 0 ? b : kBatchDefault;
 }
 
@@ -77,7 +81,7 @@ static int plan_build(const pentago_section_job *jobs, size_t n, hipStream_t str
     if (!jobs || n == 0) return fail(PENTAGO_EINVAL, "no jobs");
     if (n > 65536) return fail(PENTAGO_ERANGE, "more than 65536 jobs");
     const int stones = section_stones(jobs[0].section);
-    if (shape.cap <= 0) shape = batch_shape(stones);
+    if (shape.cap <= 0) shape = batch_shape(stones, reps);
     const int lds_cap = shape.cap;
     std::vector<SweepJob> J(n);
     for (size_t i = 0; i < n; i++) {
@@ -369,7 +373,7 @@ int pentago_autotune_sections(const pentago_section_job *jobs, size_t n, int rep
     const int stones = section_stones(jobs[0].section);
     {
         std::lock_guard<std::mutex> lock(g_shape_mutex);
-        if (stones >= 0 && stones <= 36) g_shape[stones] = best_shape;
+        if (stones >= 0 && stones <= 36) g_shape[reps != 0][stones] = best_shape;
     }
     if (cap_bytes) *cap_bytes = best_shape.cap;
     if (threads) *threads = best_shape.threads;
