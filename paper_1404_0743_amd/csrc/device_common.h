@@ -16,6 +16,15 @@
 
 namespace pg {
 
+// LDS and memory written by a lane of the wave before, read by any of its lanes
+// after: the barrier alone orders no memory.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 static __constant__ uint32_t c_pow3[10] = {1, 3, 9, 27, 81, 243, 729, 2187, 6561, 19683};
 
 // Entry offset in the 8^4-blocked layout (see pentago_section_offset).  The

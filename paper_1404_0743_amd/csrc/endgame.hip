@@ -65,13 +65,6 @@ __device__ __forceinline__ RootInfo decode_root(uint64_t packed)
     return r;
 }
 
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Five-set of one board: the colour's stones xm0 plus the empty cells of
 // subset m, stored as table entry r.  PL: the table is two planes of `smax`
 // uint4 (entry r's halves at r and smax + r), else entries of two uint4.

@@ -811,7 +811,7 @@ __device__ __forceinline__ void sweep_run_tile(const SweepJob &J, const DevTable
             L.loff[2 * J.flines + number] = line_offset_coeffs<D>(cs, with(0, (int)kid).v);
         }
         if (lane == 0) L.kid[J.fkids] = (uint32_t)nk;
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();  // L.kid and L.line are read by other lanes than wrote them
         // set vx: line vx >> 1, colour (vx & 1) + 1; from 2 nl: child line vx - 2 nl, the mover's colour
         for (int it = lane; it < 4 * (2 * nl + nk); it += 64) {
             const int vx = it >> 2, j = it & 3;
