@@ -329,7 +329,7 @@ __global__ void __launch_bounds__(256)
 __global__ void eval_clear_kernel(int *count, int *cursor, unsigned long long *counter)
 {
     if (threadIdx.x < 16) count[threadIdx.x] = cursor[threadIdx.x] = 0;
-    if (threadIdx.x < 4) counter[threadIdx.x] = 0;
+    if (threadIdx.x < kEvalCounters) counter[threadIdx.x] = 0;
 }
 
 // The whole binning of a small batch by one workgroup: for a few thousand
@@ -342,7 +342,7 @@ __global__ void __launch_bounds__(1024)
 {
     __shared__ int lc[12], base[12];
     if (threadIdx.x < 12) lc[threadIdx.x] = 0;
-    if (threadIdx.x < 4) counter[threadIdx.x] = 0;
+    if (threadIdx.x < kEvalCounters) counter[threadIdx.x] = 0;
     __syncthreads();
     int e[kBinSmall / 1024], local[kBinSmall / 1024];
 #pragma unroll
@@ -378,7 +378,16 @@ __global__ void __launch_bounds__(1024)
 // those: a launch that finds nothing to do ends without an atomic (the
 // workgroups' atomics on one counter took 39 us in a launch of 3072 waves).
 //   deepest: 9 and 10 empty cells, a workgroup per root, its layers in the
-//            workgroup's slot of a global buffer;
+//            workgroup's slot of a global buffer.  Where there are fewer slots
+//            than workgroups that run at once (the 64 of the allocation-free call)
+//            and more such roots than slots, the workgroups without a slot take
+//            single roots with 8 empty cells meanwhile: the launches behind wait
+//            for this one, and three quarters of the GPU would wait too (2000
+//            roots with 9 or 10 and 20,000 with 8 empty cells: 3.11 ms without
+//            this, 2.51 with it).  With a slot to every workgroup, or one round
+//            of roots, only the tail of the launch is idle, and roots solved
+//            one by one in it cost more than they fill (300 and 2000: 0.23 ms
+//            without, 0.25 with);
 //   class 0: 8 empty cells, a workgroup per pair of roots (155 KB of LDS);
 //   class 1: 7 empty cells, a workgroup per pair (69 KB);
 //   class 2: up to 6: a workgroup of 256 threads takes one pair of roots with
@@ -391,25 +400,50 @@ static_assert(2 * PairDag<5>::lds_bytes <= kClass2LdsBytes && 4 * PairDag<4>::ld
 
 __host__ __device__ constexpr int class2_pairs(int e) { return e == 6 ? 1 : e == 5 ? 2 : e == 4 ? 4 : 8; }
 
+// counter: [0..2] queues of the classes, [3] of the deepest roots; [4] the roots
+// with 8 empty cells taken here, the first of their bin; [5] the workgroups with a
+// layer slot that have found no deepest root left.
 template <int NT>
 __global__ void __launch_bounds__(NT)
     eval_deepest_kernel(const uint64_t *boards, const int *order, const int *start, unsigned long long *counter,
-                        uint4 *out, uint4 *gl, DevTables T)
+                        uint4 *out, uint4 *gl, int slots, DevTables T)
 {
     extern __shared__ uint4 lds[];
     __shared__ int s_item;
     __shared__ int s_slots[2][10];
-    const int n = start[8];
-    uint4 *mine = gl + (size_t)blockIdx.x * 2 * 4 * kDagGlobalLayer;
-    for (int item = blockIdx.x; item < n;) {
-        const int root = order[item];
+    const int n = start[8], eights = start[7] - n;
+    if ((int)blockIdx.x < slots) {
+        uint4 *mine = gl + (size_t)blockIdx.x * 2 * 4 * kDagGlobalLayer;
+        for (int item = blockIdx.x; item < n;) {
+            const int root = order[item];
+            const RootInfo R = decode_root(boards[root]);
+            solve_root<NT>(R, T, mine, mine + 4 * kDagGlobalLayer, kDagGlobalLayer, lds, out + 4 * (size_t)root,
+                           s_slots[0], s_slots[1]);
+            __syncthreads();
+            if (threadIdx.x == 0) s_item = slots + (int)atomicAdd(&counter[3], 1ull);
+            __syncthreads();
+            item = s_item;
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) atomicAdd(&counter[5], 1ull);
+        return;
+    }
+    if (n <= slots) return;
+    for (;;) {
+        if (threadIdx.x == 0) {
+            const bool more = __hip_atomic_load(&counter[5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+                              (unsigned long long)slots;
+            s_item = more ? (int)atomicAdd(&counter[4], 1ull) : eights;
+        }
+        __syncthreads();
+        const int item = s_item;
+        __syncthreads();
+        if (item >= eights) break;
+        const int root = order[n + item];
         const RootInfo R = decode_root(boards[root]);
-        solve_root<NT>(R, T, mine, mine + 4 * kDagGlobalLayer, kDagGlobalLayer, lds, out + 4 * (size_t)root,
-                       s_slots[0], s_slots[1]);
+        const int cap = T.dag_max[8];
+        solve_root<NT>(R, T, lds, lds + 4 * cap, cap, lds + 8 * cap, out + 4 * (size_t)root, s_slots[0], s_slots[1]);
         __syncthreads();
-        if (threadIdx.x == 0) s_item = (int)(gridDim.x + atomicAdd(&counter[3], 1ull));
-        __syncthreads();
-        item = s_item;
     }
 }
 
@@ -433,12 +467,16 @@ __global__ void __launch_bounds__(NT, CLS == 0 && NT == 512 ? 2 : 4)
 {
     extern __shared__ uint4 lds[];
     __shared__ int s_item;
+    // the first counter[4] roots with 8 empty cells were solved beside the deepest
+    // ones (read once: each read waits for the queue's atomics on the same line,
+    // 37 us in 700 with one to a pair)
+    const int solved = CLS == 0 ? (int)min(counter[4], (unsigned long long)(start[7] - start[8])) : 0;
     for (int item = blockIdx.x;;) {
         // bins are ordered by empty cells, most first: e occupies
         // [start[e], start[e - 1]), 0 ends at start[11]
         if constexpr (CLS < 2) {
             constexpr int E = 8 - CLS;
-            const int first = start[E] + 2 * item, end = start[E - 1];
+            const int first = start[E] + solved + 2 * item, end = start[E - 1];
             if (first >= end) break;
             solve_bin_chunk<E, NT, 1>(boards, order, first, end - 1, out, lds, T);
         } else {
@@ -662,7 +700,8 @@ hipError_t launch_eval_bin(const uint64_t *boards, size_t n, const EvalScratch &
     return hipGetLastError();
 }
 
-// Dynamic LDS of each class of the server's batches (launch_eval_direct).
+// Dynamic LDS of each class of the server's batches (launch_eval_direct); class
+// 0's is also that of eval_deepest_kernel.
 static int eval_class_lds_bytes(int cls)
 {
     if (cls == 0) return std::max(dag_lds_bytes(8), std::max(dag_ftab_bytes(9), dag_ftab_bytes(10)));
@@ -721,13 +760,16 @@ static hipError_t launch_pairs_class(size_t n, hipStream_t s, const uint64_t *bo
 }
 
 template <int NT>
-static hipError_t launch_deepest(size_t n, hipStream_t s, const uint64_t *boards, const EvalScratch &S, uint4 *out,
-                                 const DevTables &T)
+static hipError_t launch_deepest(size_t n, int cus, hipStream_t s, const uint64_t *boards, const EvalScratch &S,
+                                 uint4 *out, const DevTables &T)
 {
-    const unsigned g = (unsigned)std::min<size_t>(n, (size_t)S.global_slots);
-    const int lds = std::max(dag_ftab_bytes(9), dag_ftab_bytes(10));
+    // workgroups without a slot: two per CU in all, the LDS of a root with 8 empty cells
+    const unsigned g = (unsigned)std::min<size_t>(n, 2 * (size_t)cus);
+    const int lds = S.global_slots < (int)g ? eval_class_lds_bytes(0) : std::max(dag_ftab_bytes(9), dag_ftab_bytes(10));
+    const hipError_t e = allow_lds((const void *)eval_deepest_kernel<NT>, lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(eval_deepest_kernel<NT>, dim3(g), dim3(NT), lds, s, boards, S.order, S.start, S.counter, out,
-                       S.global_layers, T);
+                       S.global_layers, std::min((int)g, S.global_slots), T);
     return hipGetLastError();
 }
 
@@ -756,7 +798,7 @@ hipError_t launch_eval(const uint64_t *boards, size_t n, uint4 *out, const EvalS
     e = launch_eval_bin(boards, n, S, status, out, T, s);
     if (e != hipSuccess) return e;
     const bool c0 = g_class_threads[0] == 512, c1 = g_class_threads[1] == 512;
-    e = c0 ? launch_deepest<512>(n, s, boards, S, out, T) : launch_deepest<256>(n, s, boards, S, out, T);
+    e = c0 ? launch_deepest<512>(n, cus, s, boards, S, out, T) : launch_deepest<256>(n, cus, s, boards, S, out, T);
     if (e == hipSuccess)
         e = c0 ? launch_pairs_class<0, 1024>(n, s, boards, S, out, T) : launch_pairs_class<0, 512>(n, s, boards, S, out, T);
     if (e == hipSuccess)

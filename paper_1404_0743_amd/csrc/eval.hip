@@ -59,7 +59,7 @@ static int eval_alloc(size_t n, int grid, hipStream_t st, EvalAlloc *A)
     const size_t ints = 64;
     grid = (int)std::min<size_t>(n, (size_t)grid);  // a layer slot per workgroup, no more of them than roots
     const size_t glayer = (size_t)grid * 2 * kDagGlobalLayer * 64;
-    const size_t bytes = glayer + ints * 4 + 32 + n * 4 + n + 256;
+    const size_t bytes = glayer + ints * 4 + 64 + n * 4 + n + 256;
     hipError_t e = hipMallocAsync(&A->base, bytes, st);
     if (e != hipSuccess) return hip_fail(e, "hipMallocAsync(eval scratch)");
     char *p = (char *)A->base;
@@ -69,8 +69,9 @@ static int eval_alloc(size_t n, int grid, hipStream_t st, EvalAlloc *A)
     A->S.start = A->S.count + 16;
     A->S.cursor = A->S.count + 32;
     p += ints * 4;
-    A->S.counter = (unsigned long long *)p;  // one work-queue counter per persistent class
-    p += 32;
+    static_assert(kEvalCounters * sizeof(unsigned long long) <= 64, "queue counters");
+    A->S.counter = (unsigned long long *)p;
+    p += 64;
     A->S.order = (int *)p;
     p += n * 4;
     A->S.empties = (uint8_t *)p;

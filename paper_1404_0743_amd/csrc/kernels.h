@@ -110,13 +110,15 @@ hipError_t launch_sweep_batch(const SweepJob *dev_jobs, const long long *dev_til
                               hipStream_t s);
 
 // Endgame (Section VIII serial solver, one DAG per root).
+constexpr int kEvalCounters = 6;
+
 struct EvalScratch {
     int *count;          // [16]: per empties count 0..10, [11] invalid
     int *start;          // [16]
     int *cursor;         // [16]
     int *order;          // [n] roots sorted by empties, most first
     uint8_t *empties;    // [n]
-    unsigned long long *counter;  // work counter of the persistent launch
+    unsigned long long *counter;  // [kEvalCounters] work counters of the persistent launches
     uint4 *global_layers;         // DAG layers for roots with 9-10 empties
     int global_slots;             // number of roots the global layer buffer holds at once
 };

@@ -13,15 +13,15 @@
 
 namespace pg {
 
-// Largest batch of the allocation-free call, and the number of workgroups of
-// the 8-10 empty-cell class that own a global layer slot (the others take
-// only roots with 8 empty cells, whose layers fit in LDS).
+// Largest batch of the allocation-free call, and the number of workgroups that
+// own a global layer slot for roots with 9 or 10 empty cells (the other
+// workgroups of their launch take roots with 8, whose layers fit in LDS).
 constexpr size_t kNoAllocMaxBoards = (size_t)1 << 20;
 constexpr int kNoAllocSlots = 64;
 
 constexpr size_t kNoAllocLayerBytes = (size_t)kNoAllocSlots * 2 * 4 * kDagGlobalLayer * sizeof(uint4);
 constexpr size_t kNoAllocIntsOff = kNoAllocLayerBytes;             // count, start, cursor: 64 ints
-constexpr size_t kNoAllocCounterOff = kNoAllocIntsOff + 256;       // 4 queue counters
+constexpr size_t kNoAllocCounterOff = kNoAllocIntsOff + 256;       // queue counters
 constexpr size_t kNoAllocOrderOff = kNoAllocCounterOff + 256;      // order: int per root
 constexpr size_t kNoAllocEmptiesOff = kNoAllocOrderOff + 4 * kNoAllocMaxBoards;  // u8 per root
 constexpr size_t kNoAllocBytes = kNoAllocEmptiesOff + kNoAllocMaxBoards;
@@ -96,9 +96,9 @@ int pentago_eval_batch_noalloc(const pentago_board *boards, size_t n, pentago_su
     S.empties = (uint8_t *)(base + kNoAllocEmptiesOff);
     S.global_slots = std::min(kNoAllocSlots, grid);
     const hipStream_t st = (hipStream_t)hip_stream;
-    // the binning pass clears the per-class counts and the persistent launch
-    // its queue counters with small kernels: nothing from an earlier call is
-    // read before it is rewritten
+    // the binning pass clears the counts and queue counters with small kernels
+    // (a few boards take one launch that uses neither): nothing from an earlier
+    // call is read before it is rewritten
     e = launch_eval((const uint64_t *)boards, n, (uint4 *)out, S, status, T, st);
     if (e != hipSuccess) return hip_fail(e, "eval launch");
     return 0;
