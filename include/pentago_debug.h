@@ -50,6 +50,12 @@ int pentago_debug_sym_pattern(int sym, int black, int white, int index, int *src
  * code to it (Section IV). */
 int pentago_debug_canon(int code, int *index, int *k);
 
+/* How pentago_solve_section (reps nonzero: pentago_solve_section_d4) lays out
+ * section s in this process: lines per tile, threads and tile order, and in
+ * *siblings 1 if its tiles are lines of sibling patterns (shape->lines is then
+ * the most lines of a tile).  Uses no GPU. */
+int pentago_debug_layout(pentago_section s, int reps, pentago_tile_shape *shape, int *siblings);
+
 #ifdef __cplusplus
 }
 #endif

@@ -205,6 +205,15 @@ void section_shape_of(const pentago_section &s, int m[4])
     for (int j = 0; j < 4; j++) m[j] = H.class_size[s.black[j]][s.white[j]];
 }
 
+// Tiles of G lines.
+static void set_lines(SweepJob *J, int G)
+{
+    J->G = G;
+    J->ngroups = (J->m[J->e] + G - 1) / G;
+    J->ntiles = (long long)J->m[J->o1] * J->m[J->o2] * J->ngroups;
+    J->lds_bytes = sweep_lds_bytes(G, J->m[J->d], (J->emask >> J->d) & 1 ? J->cm[J->d] : 0);
+}
+
 // Build the sweep job of one section.  `force_d` >= 0 picks the staged
 // dimension; G > 0 the lines per tile, force_threads > 0 the workgroup
 // size and force_order >= 0 the tile order (for the tile autotuner).
@@ -278,10 +287,7 @@ int make_job(const pentago_section &s, const pentago_superinfo *const child[4],
     if (forceG > 0) G = forceG;
     else if (tuned.lines > 0) G = tuned.lines;
     else while (G > 1 && sweep_lds_bytes(G, J->m[J->d], cmd) > 40960) G--;
-    J->G = G;
-    J->ngroups = (J->m[J->e] + G - 1) / G;
-    J->ntiles = (long long)J->m[J->o1] * J->m[J->o2] * J->ngroups;
-    J->lds_bytes = sweep_lds_bytes(G, J->m[J->d], cmd);
+    set_lines(J, G);
     J->out = (uint4 *)out;
     J->fam = -1;
     return 0;
@@ -350,6 +356,42 @@ bool make_run(const pentago_section &s, SweepJob *J, int lds_cap)
         return true;
     }
     return false;
+}
+
+// The sweep of one section as the library lays it out (reps: its children are
+// held as their representatives).
+int plan_section(const pentago_section &s, const pentago_superinfo *const child[4], pentago_superinfo *out,
+                 bool reps, SweepJob *J)
+{
+    int rc = make_job(s, child, out, J, -1, 0);
+    if (rc) return rc;
+    if (reps) set_child_syms(s, child, J);
+    take_siblings(s, J);
+    if (J->fam >= 0 || !J->csym[J->d]) return 0;
+    // The staged child is read through a symmetry: the kernel needs more
+    // registers (two 512-thread workgroups per CU), and shapes sized for the plain
+    // one do not suit it.  Untuned: 256 threads, 32 KiB, natural order (over 129
+    // sections of 32 to 35 stones and 2,000 to 8 million entries 1.06 of the
+    // best shape's time in the mean; 256 threads and 64 KiB 1.17, the plain
+    // rule's 512 threads 1.13, and up to 1.9 times the 256 threads').  32 KiB
+    // may hold one line only; two, if 52 KiB do, are as fast or faster.  With a shape
+    // tuned for the plain sweep, 7 lines (on the 6,288,640-entry section with 160
+    // patterns to a line 148 us against 179 with the tuned 5; 8 lines gave 176).
+    const int mD = J->m[J->d], cmd = J->cm[J->d];
+    auto lines = [&](int most, int lds) {
+        while (most > 1 && sweep_lds_bytes(most, mD, cmd) > lds) most--;
+        return most;
+    };
+    const TileShape tuned = tuned_tile_shape(*J);
+    if (tuned.lines > 0) {
+        if (tuned.threads == 512) set_lines(J, std::max(lines(7, 65536), J->G));
+    } else {
+        const int G = lines(8, 32768);
+        set_lines(J, G > 1 ? G : lines(8, 53248));
+        J->threads = 256;
+        J->order = 0;
+    }
+    return 0;
 }
 
 size_t prep_bytes(const SweepJob &J, int j)
@@ -427,9 +469,8 @@ int pentago_solve_section(pentago_section s, const pentago_superinfo *const chil
     int rc = device_tables(&T);
     if (rc) return rc;
     SweepJob J;
-    rc = make_job(s, child, out, &J, -1, 0);
+    rc = plan_section(s, child, out, false, &J);
     if (rc) return rc;
-    take_siblings(s, &J);
     rc = validate_children(J, (hipStream_t)hip_stream);
     if (rc) return rc;
     return run_job(J, T, (hipStream_t)hip_stream);

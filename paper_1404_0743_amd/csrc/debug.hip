@@ -80,6 +80,22 @@ int pentago_debug_sym_pattern(int sym, int black, int white, int index, int *src
     return 0;
 }
 
+int pentago_debug_layout(pentago_section s, int reps, pentago_tile_shape *shape, int *siblings)
+{
+    if (!shape || !siblings) return fail(PENTAGO_EINVAL, "NULL argument");
+    // addresses that no table has (nothing is read): out and the children lie
+    // further apart than the largest table is long
+    pentago_superinfo *out = (pentago_superinfo *)((uintptr_t)1 << 60);
+    const pentago_superinfo *child[4];
+    for (int j = 0; j < 4; j++) child[j] = (const pentago_superinfo *)((uintptr_t)(j + 1) << 50);
+    SweepJob J;
+    const int rc = plan_section(s, child, out, reps != 0, &J);
+    if (rc) return rc;
+    *siblings = J.fam >= 0;
+    *shape = *siblings ? pentago_tile_shape{J.flines, J.threads, 1} : pentago_tile_shape{J.G, J.threads, J.order};
+    return 0;
+}
+
 int pentago_debug_canon(int code, int *index, int *k)
 {
     if (code < 0 || code >= 19683 || !index || !k) return fail(PENTAGO_EINVAL, "invalid arguments");

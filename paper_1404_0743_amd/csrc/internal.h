@@ -42,6 +42,8 @@ constexpr int kRunLdsCap = 53248;  // LDS of a tile of sibling lines: three work
 bool make_run(const pentago_section &s, SweepJob *J, int lds_cap);
 // make_run where it is the faster layout (after set_child_syms, if that is used)
 void take_siblings(const pentago_section &s, SweepJob *J);
+int plan_section(const pentago_section &s, const pentago_superinfo *const child[4], pentago_superinfo *out,
+                 bool reps, SweepJob *J);
 TileShape tuned_tile_shape(const SweepJob &J);
 void remember_tile_shape(const SweepJob &J, TileShape t);
 pentago_section section_image(const pentago_section &s, int sym);

@@ -109,6 +109,7 @@ _SIGS = {
     "pentago_debug_sym": ([_P, ctypes.c_int, _P, _P], ctypes.c_int),
     "pentago_debug_sym_pattern": ([ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, _P, _P],
                                   ctypes.c_int),
+    "pentago_debug_layout": ([Section, ctypes.c_int, _P, _P], ctypes.c_int),
     "pentago_debug_swap3": ([_P, ctypes.c_int, _P], ctypes.c_int),
 }
 
@@ -552,3 +553,11 @@ def pentago_debug_canon(code):
     i, k = ctypes.c_int(), ctypes.c_int()
     _check(lib().pentago_debug_canon(code, ctypes.byref(i), ctypes.byref(k)), "pentago_debug_canon")
     return i.value, k.value
+
+
+def pentago_debug_layout(counts, reps=False):
+    """({"lines", "threads", "order"}, siblings) of a single section's sweep."""
+    shape, sib = TileShape(), ctypes.c_int()
+    _check(lib().pentago_debug_layout(section(counts), 1 if reps else 0, ctypes.byref(shape), ctypes.byref(sib)),
+           "pentago_debug_layout")
+    return {"lines": shape.lines, "threads": shape.threads, "order": shape.order}, bool(sib.value)

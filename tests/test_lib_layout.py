@@ -1,0 +1,33 @@
+"""CPU checks of the layout a single section's sweep takes when nothing was
+tuned, at sections whose layouts were timed against one another: the layout
+that another rule would take there was slower by the factor noted."""
+import pytest
+
+from paper_1404_0743_amd import inputs as I
+from paper_1404_0743_amd import pentago as P
+
+
+def counts_of(text):
+    return tuple((int(text[2 * j]), int(text[2 * j + 1])) for j in range(4))
+
+
+# 512 threads took 1.9, 1.6, 1.4, 1.4, 1.3, 1.3 and 1.25 times as long
+THROUGH_SYMMETRY = ["54459008", "07544481", "62635418", "53177036", "36623663", "50454536", "44078144"]
+
+
+@pytest.mark.parametrize("counts", THROUGH_SYMMETRY)
+def test_staged_representative_takes_256_threads(counts):
+    shape, siblings = P.pentago_debug_layout(counts_of(counts), reps=True)
+    assert not siblings
+    assert shape["threads"] == 256 and shape["order"] == 0
+    assert 1 <= shape["lines"] <= 8
+
+
+def test_layouts_are_in_range():
+    """Every layout stays inside what pentago_solve_section_shape accepts."""
+    for stones in (32, 33, 34, 35):
+        for s in I.all_sections(stones)[::17]:
+            for reps in (False, True):
+                shape, siblings = P.pentago_debug_layout(s, reps)
+                assert shape["threads"] in (256, 512) and shape["order"] in (0, 1)
+                assert 1 <= shape["lines"] <= (10 if siblings else 8)
