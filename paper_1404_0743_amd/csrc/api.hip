@@ -276,17 +276,32 @@ int make_job(const pentago_section &s, const pentago_superinfo *const child[4],
     const int cmd = (J->emask >> J->d) & 1 ? J->cm[J->d] : 0;
     // lines per tile: at most 8 (one 8^4 block row), the tile's LDS within 40
     // KiB, so that four 512-thread workgroups share a CU, and a contiguous range
-    // of tiles per XCD.  Timed against every shape over 36 sections of 33 to 35
-    // stones and 3,000 to 12 million entries: 1.06 of the best shape's time in
-    // the mean, 1.37 at worst (32 KiB 1.09, 52 KiB 1.08, 256 threads 1.09 at
-    // their best cap; 256 threads and 64 KiB, the rule before, 1.25 and 1.73)
-    int G = 8;
+    // of tiles per XCD.  Where that holds one line only (160 child patterns and
+    // more), two at 52 KiB share the positions' tables: 15 million entries in lines
+    // of 318 patterns 732 us against 958, 8 million 188 against 237.  Where a
+    // tile has at most 256 parents, 256 threads and 32 KiB: 2.7 million entries
+    // in lines of 10 411 us against 445.  Timed against every shape over 224
+    // sections of 32 to 35 stones and 2,000 to 15 million entries: 1.04 of the
+    // best shape's time in the mean, 1.30 at worst (without the two exceptions
+    // 1.045 and 1.38; 256 threads 1.06 and 1.48 at their best cap; 256 threads,
+    // 64 KiB and natural order 1.19 and 2.26)
+    auto lines = [&](int lds) {
+        int g = 8;
+        while (g > 1 && sweep_lds_bytes(g, J->m[J->d], cmd) > lds) g--;
+        return g;
+    };
     const TileShape tuned = tuned_tile_shape(*J);
-    J->threads = force_threads > 0 ? force_threads : tuned.lines > 0 ? tuned.threads : 512;
+    int G = forceG > 0 ? forceG : tuned.lines, threads = tuned.lines > 0 ? tuned.threads : 512;
+    if (G <= 0) {
+        G = lines(40960);
+        if (G == 1) G = lines(53248);
+        if (J->emask && G * J->m[J->d] <= 256) {  // (full boards take the terminal kernel)
+            threads = 256;
+            G = lines(32768);
+        }
+    }
+    J->threads = force_threads > 0 ? force_threads : threads;
     J->order = force_order >= 0 ? force_order : tuned.lines > 0 ? tuned.order : 1;
-    if (forceG > 0) G = forceG;
-    else if (tuned.lines > 0) G = tuned.lines;
-    else while (G > 1 && sweep_lds_bytes(G, J->m[J->d], cmd) > 40960) G--;
     set_lines(J, G);
     J->out = (uint4 *)out;
     J->fam = -1;

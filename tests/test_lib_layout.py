@@ -31,3 +31,15 @@ def test_layouts_are_in_range():
                 shape, siblings = P.pentago_debug_layout(s, reps)
                 assert shape["threads"] in (256, 512) and shape["order"] in (0, 1)
                 assert 1 <= shape["lines"] <= (10 if siblings else 8)
+
+
+@pytest.mark.parametrize("counts,lines,threads", [
+    ("62364345", 2, 512),   # 318 patterns and 160 children to a line: one line took 1.3 times as long
+    ("34454563", 2, 512),   # the same, 1.26
+    ("34632763", 2, 512),   # the same, 1.12
+    ("70452635", 8, 256),   # 80 parents to a tile: 512 threads took 1.08
+])
+def test_plain_lines(counts, lines, threads):
+    shape, siblings = P.pentago_debug_layout(counts_of(counts))
+    assert not siblings
+    assert shape == {"lines": lines, "threads": threads, "order": 1}
