@@ -279,12 +279,13 @@ int make_job(const pentago_section &s, const pentago_superinfo *const child[4],
     // of tiles per XCD.  Where that holds one line only (160 child patterns and
     // more), two at 52 KiB share the positions' tables: 15 million entries in lines
     // of 318 patterns 732 us against 958, 8 million 188 against 237.  Where a
-    // tile has at most 256 parents, 256 threads and 32 KiB: 2.7 million entries
-    // in lines of 10 411 us against 445.  Timed against every shape over 224
-    // sections of 32 to 35 stones and 2,000 to 15 million entries: 1.04 of the
-    // best shape's time in the mean, 1.30 at worst (without the two exceptions
-    // 1.045 and 1.38; 256 threads 1.06 and 1.48 at their best cap; 256 threads,
-    // 64 KiB and natural order 1.19 and 2.26)
+    // tile has at most 128 parents (lines of 10), a quarter of 512 threads, 256
+    // threads and 32 KiB: 2.7 million entries 411 us against 445 (with 176
+    // parents, lines of 22, it goes either way: 146 us against 126, 94 against 99).
+    // Timed against every shape over 342 sections of 32 to 35 stones and 2,000 to
+    // 15 million entries: 1.03 of the best shape's time in the mean, 1.38 at worst
+    // (without the two exceptions 1.045 and 1.38; 256 threads 1.06 and 1.48 at
+    // their best cap; 256 threads, 64 KiB and natural order 1.19 and 2.26)
     auto lines = [&](int lds) {
         int g = 8;
         while (g > 1 && sweep_lds_bytes(g, J->m[J->d], cmd) > lds) g--;
@@ -295,7 +296,7 @@ int make_job(const pentago_section &s, const pentago_superinfo *const child[4],
     if (G <= 0) {
         G = lines(40960);
         if (G == 1) G = lines(53248);
-        if (J->emask && G * J->m[J->d] <= 256) {  // (full boards take the terminal kernel)
+        if (J->emask && G * J->m[J->d] <= 128) {  // (full boards take the terminal kernel)
             threads = 256;
             G = lines(32768);
         }

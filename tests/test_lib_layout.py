@@ -38,6 +38,8 @@ def test_layouts_are_in_range():
     ("34454563", 2, 512),   # the same, 1.26
     ("34632763", 2, 512),   # the same, 1.12
     ("70452635", 8, 256),   # 80 parents to a tile: 512 threads took 1.08
+    ("36443660", 8, 512),   # 176 parents to a tile: 256 threads took 1.16
+    ("72450663", 8, 512),   # the same, 1.41
 ])
 def test_plain_lines(counts, lines, threads):
     shape, siblings = P.pentago_debug_layout(counts_of(counts))
