@@ -311,11 +311,15 @@ int make_job(const pentago_section &s, const pentago_superinfo *const child[4],
 
 // Small sections go in tiles of sibling lines, unless tiles of lines were tuned
 // to be faster: they save the prep launch and its scratch (25,000 entries: 9 us
-// against 28; 0.14 million 19 against 34, 0.9 million 51 against 64).  Beyond a
-// million entries the prep launch no longer shows, and tiles of lines, more
-// parents to a table, are as fast or faster (4 to 12 million entries: 0.74 to
-// 1.26 of the siblings' time, 0.96 in the mean).  The two staged children must
-// be held as themselves.
+// against 28; 0.14 million 19 against 34, 0.9 million 51 against 64).  In more
+// than 16 rounds of the GPU's 256 CUs, or beyond a million entries, the prep
+// launch no longer shows, and tiles of lines, more parents to a table, are as
+// fast or faster.  The siblings' time over that of lines, 153 sections of 32 to
+// 35 stones, mean and range:
+//   up to 2^20 entries   to 1024 tiles 0.48 (0.30-1.00), to 4096 0.81 (0.56-1.10),
+//                        beyond 1.28 (1.08-1.47)
+//   beyond               1.10 (0.88-1.63)
+// The two staged children must be held as themselves.
 void take_siblings(const pentago_section &s, SweepJob *J)
 {
     const TileShape tuned = tuned_tile_shape(*J);
@@ -323,7 +327,8 @@ void take_siblings(const pentago_section &s, SweepJob *J)
     for (int j = 0; j < 4; j++) entries *= (uint64_t)J->m[j];
     if (tuned.lines > 0 ? !tuned.runs : entries > (1u << 20)) return;
     SweepJob R = *J;
-    if (make_run(s, &R, kRunLdsCap) && !R.csym[R.d] && !R.csym[R.fam]) *J = R;
+    if (!make_run(s, &R, kRunLdsCap) || R.csym[R.d] || R.csym[R.fam]) return;
+    if (tuned.lines > 0 || R.ntiles <= 4096) *J = R;
 }
 
 // Lay J out in tiles of sibling lines if its section has empty cells in two

@@ -45,3 +45,16 @@ def test_plain_lines(counts, lines, threads):
     shape, siblings = P.pentago_debug_layout(counts_of(counts))
     assert not siblings
     assert shape == {"lines": lines, "threads": threads, "order": 1}
+
+
+@pytest.mark.parametrize("counts,want", [
+    ("63810835", True),     # 25,000 entries, a few hundred tiles: lines took 3 times as long
+    ("63531853", True),     # 1,047,816 entries, 1452 tiles: 1.5
+    ("71074553", False),    # 771,120 entries in 12,240 tiles: siblings took 1.3 times as long
+    ("35703645", False),    # 942,480 entries in 14,960 tiles: 1.25
+    ("70442745", False),    # 544,000 entries in 10,200 tiles: 1.3
+    ("72545307", False),    # 428,400 entries in 5440 tiles: 1.1
+    ("07634462", False),    # beyond 2^20 entries
+])
+def test_sibling_tiles_where_they_are_few(counts, want):
+    assert P.pentago_debug_layout(counts_of(counts))[1] == want
