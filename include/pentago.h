@@ -188,7 +188,11 @@ typedef struct {
  * events on hip_stream, remembers the fastest for this section geometry
  * (later pentago_solve_section calls with the same geometry use it;
  * pentago_solve_sections uses its lines per tile) and leaves out holding the
- * sweep's result.  Synchronises the stream.  shape and best_ms may be NULL. */
+ * sweep's result.  shape and best_ms are that shape and its time, as
+ * pentago_solve_section_shape takes it.  Where tiles of sibling lines, a layout
+ * without a shape, are faster still, that is remembered too, and later
+ * pentago_solve_section calls take less than best_ms.  Synchronises the stream.
+ * shape and best_ms may be NULL. */
 int pentago_autotune_section(pentago_section s, const pentago_superinfo *const child[4],
                              pentago_superinfo *out, void *hip_stream, pentago_tile_shape *shape,
                              float *best_ms);

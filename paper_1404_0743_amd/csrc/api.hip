@@ -309,8 +309,8 @@ int make_job(const pentago_section &s, const pentago_superinfo *const child[4],
     return 0;
 }
 
-// Small sections go in tiles of sibling lines, unless tiles of lines were tuned
-// to be faster: they save the prep launch and its scratch (25,000 entries: 9 us
+// Small sections go in tiles of sibling lines, unless the autotuner found tiles
+// of lines faster: they save the prep launch and its scratch (25,000 entries: 9 us
 // against 28; 0.14 million 19 against 34, 0.9 million 51 against 64).  In more
 // than 16 rounds of the GPU's 256 CUs, or beyond a million entries, the prep
 // launch no longer shows, and tiles of lines, more parents to a table, are as
@@ -322,13 +322,12 @@ int make_job(const pentago_section &s, const pentago_superinfo *const child[4],
 // The two staged children must be held as themselves.
 void take_siblings(const pentago_section &s, SweepJob *J)
 {
-    const TileShape tuned = tuned_tile_shape(*J);
-    uint64_t entries = 1;
-    for (int j = 0; j < 4; j++) entries *= (uint64_t)J->m[j];
-    if (tuned.lines > 0 ? !tuned.runs : entries > (1u << 20)) return;
     SweepJob R = *J;
     if (!make_run(s, &R, kRunLdsCap) || R.csym[R.d] || R.csym[R.fam]) return;
-    if (tuned.lines > 0 || R.ntiles <= 4096) *J = R;
+    const int tuned = tuned_siblings(*J, R);
+    uint64_t entries = 1;
+    for (int j = 0; j < 4; j++) entries *= (uint64_t)J->m[j];
+    if (tuned >= 0 ? tuned == 1 : entries <= (1u << 20) && R.ntiles <= 4096) *J = R;
 }
 
 // Lay J out in tiles of sibling lines if its section has empty cells in two

@@ -30,13 +30,11 @@ int run_job(SweepJob &J, const DevTables &T, hipStream_t st);
 // With pentago_set_validate(1): EINVAL unless every child table J reads has
 // each entry's win set inside its not-lose set (synchronises st); else 0.
 int validate_children(const SweepJob &J, hipStream_t st);
-// Tile shape of a section geometry chosen by the autotuner (0 lines: none);
-// runs: tiles of sibling lines (make_run) were faster than the best of these.
+// Tile shape of a section geometry chosen by the autotuner (0 lines: none).
 struct TileShape {
     int lines;
     int threads;
     int order;
-    bool runs;
 };
 constexpr int kRunLdsCap = 53248;  // LDS of a tile of sibling lines: three workgroups per CU
 bool make_run(const pentago_section &s, SweepJob *J, int lds_cap);
@@ -46,6 +44,9 @@ int plan_section(const pentago_section &s, const pentago_superinfo *const child[
                  bool reps, SweepJob *J);
 TileShape tuned_tile_shape(const SweepJob &J);
 void remember_tile_shape(const SweepJob &J, TileShape t);
+// Whether the autotuner found tiles of sibling lines (make_run) faster than the
+// best tiles of lines: 1 or 0, -1 if it has not timed them.
+int tuned_siblings(const SweepJob &lines, const SweepJob &siblings);
 pentago_section section_image(const pentago_section &s, int sym);
 void section_standardize(const pentago_section &s, pentago_section *rep, int *sym);
 void set_child_syms(const pentago_section &s, const pentago_superinfo *const rep[4], SweepJob *J);

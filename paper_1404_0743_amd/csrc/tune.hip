@@ -25,7 +25,30 @@ TileShape tuned_tile_shape(const SweepJob &J)
 {
     std::lock_guard<std::mutex> lock(g_tune_mutex);
     auto it = g_tile_cache.find(tile_key(J));
-    return it == g_tile_cache.end() ? TileShape{0, 0, 0, false} : it->second;
+    return it == g_tile_cache.end() ? TileShape{0, 0, 0} : it->second;
+}
+
+// Tiles of sibling lines also depend on the runs of their quadrant's class:
+// sections of equal extents may have other runs.
+using SiblingKey = std::tuple<TileKey, int, int>;
+static std::map<SiblingKey, bool> g_sibling_cache;
+
+static SiblingKey sibling_key(const SweepJob &lines, const SweepJob &siblings)
+{
+    return SiblingKey(tile_key(lines), siblings.fam, siblings.frun);
+}
+
+int tuned_siblings(const SweepJob &lines, const SweepJob &siblings)
+{
+    std::lock_guard<std::mutex> lock(g_tune_mutex);
+    auto it = g_sibling_cache.find(sibling_key(lines, siblings));
+    return it == g_sibling_cache.end() ? -1 : (int)it->second;
+}
+
+static void remember_siblings(const SweepJob &lines, const SweepJob &siblings, bool faster)
+{
+    std::lock_guard<std::mutex> lock(g_tune_mutex);
+    g_sibling_cache[sibling_key(lines, siblings)] = faster;
 }
 
 void remember_tile_shape(const SweepJob &J, TileShape t)
@@ -72,7 +95,7 @@ extern "C" int pentago_autotune_section(pentago_section s, const pentago_superin
     hipEvent_t a, b;
     if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess)
         return fail(PENTAGO_EDEVICE, "hipEventCreate");
-    TileShape best_shape{0, 0, 0, false};
+    TileShape best_shape{0, 0, 0};
     float best = 1e30f;
     auto time = [&](SweepJob &J) {
         rc = run_job(J, T, st);  // warm-up
@@ -97,23 +120,19 @@ extern "C" int pentago_autotune_section(pentago_section s, const pentago_superin
                 const float t = time(J);
                 if (rc == 0 && t < best) {
                     best = t;
-                    best_shape = TileShape{G, nt, order, false};
+                    best_shape = TileShape{G, nt, order};
                 }
             }
         }
     }
     SweepJob Jr = J0;
-    if (rc == 0 && make_run(s, &Jr, kRunLdsCap)) {
-        const float t = time(Jr);
-        if (rc == 0 && t < best) {
-            best = t;
-            best_shape.runs = true;
-        }
-    }
+    const bool siblings = rc == 0 && make_run(s, &Jr, kRunLdsCap);
+    const float sibling_ms = siblings ? time(Jr) : 0;
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
     if (rc) return rc;
     remember_tile_shape(J0, best_shape);
+    if (siblings) remember_siblings(J0, Jr, sibling_ms < best);
     // leave out holding the result of the chosen shape
     SweepJob J;
     rc = make_job(s, child, out, &J, -1, 0);
