@@ -412,6 +412,7 @@ __global__ void __launch_bounds__(NT)
     __shared__ int s_item;
     __shared__ int s_slots[2][10];
     const int n = start[8], eights = start[7] - n;
+    const bool share = n > slots && (int)gridDim.x > slots;  // (no atomic without need: 512 of them take 2 us)
     if ((int)blockIdx.x < slots) {
         uint4 *mine = gl + (size_t)blockIdx.x * 2 * 4 * kDagGlobalLayer;
         for (int item = blockIdx.x; item < n;) {
@@ -425,10 +426,10 @@ __global__ void __launch_bounds__(NT)
             item = s_item;
             __syncthreads();
         }
-        if (threadIdx.x == 0) atomicAdd(&counter[5], 1ull);
+        if (share && threadIdx.x == 0) atomicAdd(&counter[5], 1ull);
         return;
     }
-    if (n <= slots) return;
+    if (!share) return;
     for (;;) {
         if (threadIdx.x == 0) {
             const bool more = __hip_atomic_load(&counter[5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
