@@ -307,10 +307,13 @@ int pentago_eval_batch(const pentago_board *boards, size_t n, pentago_superinfo 
                        int32_t *status, void *hip_stream);
 
 /* The endgame autotuner: times pentago_eval_batch on these boards with 256
- * and 512 threads per root for the workgroup-per-root classes (8-10 and 7
- * empty cells) and keeps the fastest pair for later calls (process-wide).
- * Leaves out holding the result; synchronises the stream.  threads (2 ints)
- * and best_ms may be NULL.  Errors as pentago_eval_batch. */
+ * and 512 threads per root with 9 or 10, with 8 and with 7 empty cells (the last
+ * two are solved in pairs of twice as many) and keeps the faster of each for
+ * later calls (process-wide) where it gains more than 2 %: a batch without such
+ * roots, or one of so few boards that it is not binned, changes nothing.
+ * Leaves out holding the result; synchronises the stream.  threads (2 ints:
+ * for 8 and for 7 empty cells) and best_ms may be NULL.  Errors as
+ * pentago_eval_batch. */
 int pentago_autotune_eval(const pentago_board *boards, size_t n, pentago_superinfo *out, void *hip_stream,
                           int threads[2], float *best_ms);
 

@@ -50,6 +50,11 @@ int pentago_debug_sym_pattern(int sym, int black, int white, int index, int *src
  * code to it (Section IV). */
 int pentago_debug_canon(int code, int *index, int *k);
 
+/* Threads per root (256 or 512) with 9 or 10, with 8 and with 7 empty cells: as
+ * they are in this process into get, then those of set (each may be NULL).
+ * EINVAL for other numbers in set.  Uses no GPU. */
+int pentago_debug_eval_threads(const int set[3], int get[3]);
+
 /* How pentago_solve_section (reps nonzero: pentago_solve_section_d4) lays out
  * section s in this process: lines per tile, threads and tile order, and in
  * *siblings 1 if its tiles are lines of sibling patterns (shape->lines is then

@@ -80,6 +80,17 @@ int pentago_debug_sym_pattern(int sym, int black, int white, int index, int *src
     return 0;
 }
 
+int pentago_debug_eval_threads(const int set[3], int get[3])
+{
+    for (int c = 0; c < kEvalThreadClasses; c++)
+        if (set && set[c] != 256 && set[c] != 512) return fail(PENTAGO_EINVAL, "threads per root: 256 or 512");
+    for (int c = 0; c < kEvalThreadClasses; c++) {
+        if (get) get[c] = get_eval_class_threads(c);
+        if (set) set_eval_class_threads(c, set[c]);
+    }
+    return 0;
+}
+
 int pentago_debug_layout(pentago_section s, int reps, pentago_tile_shape *shape, int *siblings)
 {
     if (!shape || !siblings) return fail(PENTAGO_EINVAL, "NULL argument");

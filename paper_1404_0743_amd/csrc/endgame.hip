@@ -3,6 +3,8 @@
 #include "device_common.h"
 #include "pairs.h"
 
+#include <atomic>
+
 namespace pg {
 
 // ---------------------------------------------------------------------------
@@ -717,21 +719,11 @@ static hipError_t allow_lds(const void *kernel, int bytes)
     return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
-// Threads per root of 8 to 10 and of 7 empty cells (256 or 512): a pair of
-// roots with 8 or 7 takes twice as many.
-static int g_class_threads[2] = {512, 256};
+static std::atomic<int> g_class_threads[kEvalThreadClasses] = {{512}, {512}, {256}};
 
-void set_eval_class_threads(int c0, int c1)
-{
-    g_class_threads[0] = c0;
-    g_class_threads[1] = c1;
-}
+void set_eval_class_threads(int cls, int threads) { g_class_threads[cls] = threads; }
 
-void get_eval_class_threads(int *c0, int *c1)
-{
-    *c0 = g_class_threads[0];
-    *c1 = g_class_threads[1];
-}
+int get_eval_class_threads(int cls) { return g_class_threads[cls]; }
 
 // Persistent grid: the kernel's occupancy times the CU count, or a workgroup
 // per item if there are fewer.
@@ -787,6 +779,8 @@ static hipError_t launch_few(const uint64_t *boards, size_t n, uint4 *out, const
     return hipGetLastError();
 }
 
+int eval_few_boards(int cus, int slots) { return std::min(cus, slots); }
+
 hipError_t launch_eval(const uint64_t *boards, size_t n, uint4 *out, const EvalScratch &S, int *status,
                        const DevTables &T, hipStream_t s)
 {
@@ -795,11 +789,11 @@ hipError_t launch_eval(const uint64_t *boards, size_t n, uint4 *out, const EvalS
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
-    if (n <= (size_t)std::min(cus, S.global_slots)) return launch_few(boards, n, out, S, status, T, s);
+    if (n <= (size_t)eval_few_boards(cus, S.global_slots)) return launch_few(boards, n, out, S, status, T, s);
     e = launch_eval_bin(boards, n, S, status, out, T, s);
     if (e != hipSuccess) return e;
-    const bool c0 = g_class_threads[0] == 512, c1 = g_class_threads[1] == 512;
-    e = c0 ? launch_deepest<512>(n, cus, s, boards, S, out, T) : launch_deepest<256>(n, cus, s, boards, S, out, T);
+    const bool cd = g_class_threads[0] == 512, c0 = g_class_threads[1] == 512, c1 = g_class_threads[2] == 512;
+    e = cd ? launch_deepest<512>(n, cus, s, boards, S, out, T) : launch_deepest<256>(n, cus, s, boards, S, out, T);
     if (e == hipSuccess)
         e = c0 ? launch_pairs_class<0, 1024>(n, s, boards, S, out, T) : launch_pairs_class<0, 512>(n, s, boards, S, out, T);
     if (e == hipSuccess)

@@ -142,39 +142,47 @@ int pentago_autotune_eval(const pentago_board *boards, size_t n, pentago_superin
     if (n > (size_t)1 << 30) return fail(PENTAGO_ERANGE, "more than 2^30 boards");
     if (n == 0) return 0;
     const hipStream_t st = (hipStream_t)hip_stream;
+    int dev = 0, cus = 0, grid = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
+    int rc = eval_grid(&grid);
+    if (rc) return rc;
     hipEvent_t a, b;
     if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess)
         return fail(PENTAGO_EDEVICE, "hipEventCreate");
-    int best0 = 0, best1 = 0, rc = 0;
-    float best = 1e30f;
-    for (int c0 = 256; c0 <= 512 && rc == 0; c0 *= 2)
-        for (int c1 = 256; c1 <= 512 && rc == 0; c1 *= 2) {
-            set_eval_class_threads(c0, c1);
-            rc = pentago_eval_batch(boards, n, out, nullptr, hip_stream);  // warm-up
-            float t = 1e30f;
-            for (int rep = 0; rep < 3 && rc == 0; rep++) {
-                (void)hipEventRecord(a, st);
-                rc = pentago_eval_batch(boards, n, out, nullptr, hip_stream);
-                (void)hipEventRecord(b, st);
-                if (hipEventSynchronize(b) != hipSuccess) rc = fail(PENTAGO_EDEVICE, "hipEventSynchronize");
-                float ms = 0;
-                (void)hipEventElapsedTime(&ms, a, b);
-                t = std::min(t, ms);
-            }
-            if (rc == 0 && t < best) {
-                best = t;
-                best0 = c0;
-                best1 = c1;
-            }
+    auto time = [&] {
+        rc = pentago_eval_batch(boards, n, out, nullptr, hip_stream);  // warm-up
+        float t = 1e30f;
+        for (int rep = 0; rep < 3 && rc == 0; rep++) {
+            (void)hipEventRecord(a, st);
+            rc = pentago_eval_batch(boards, n, out, nullptr, hip_stream);
+            (void)hipEventRecord(b, st);
+            if (hipEventSynchronize(b) != hipSuccess) rc = fail(PENTAGO_EDEVICE, "hipEventSynchronize");
+            float ms = 0;
+            (void)hipEventElapsedTime(&ms, a, b);
+            t = std::min(t, ms);
         }
+        return t;
+    };
+    float best = time();
+    // The classes' launches follow one another, so each size is tried by itself.
+    // A batch that goes without binning has none of them, and one without roots
+    // of a class times only noise: a size changes where it gains 2 %.
+    const bool binned = n > (size_t)eval_few_boards(cus, (int)std::min<size_t>(n, (size_t)grid));
+    for (int cls = 0; cls < kEvalThreadClasses && binned && rc == 0; cls++) {
+        const int kept = get_eval_class_threads(cls);
+        set_eval_class_threads(cls, 768 - kept);
+        const float t = time();
+        if (rc == 0 && t < 0.98f * best) best = t;
+        else set_eval_class_threads(cls, kept);
+    }
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
     if (rc) return rc;
-    set_eval_class_threads(best0, best1);
-    rc = pentago_eval_batch(boards, n, out, nullptr, hip_stream);
     if (threads) {
-        threads[0] = best0;
-        threads[1] = best1;
+        threads[0] = get_eval_class_threads(1);
+        threads[1] = get_eval_class_threads(2);
     }
     if (best_ms) *best_ms = best;
     return rc;

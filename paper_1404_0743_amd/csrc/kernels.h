@@ -131,10 +131,14 @@ hipError_t launch_eval_bin(const uint64_t *boards, size_t n, const EvalScratch &
 // status: incremented once per board that is invalid (its output is zero).
 hipError_t launch_eval(const uint64_t *boards, size_t n, uint4 *out, const EvalScratch &S, int *status,
                        const DevTables &T, hipStream_t s);
-// Threads per root with 8 to 10 and with 7 empty cells (256 or 512), set by the
-// endgame autotuner; process-wide.
-void set_eval_class_threads(int c0, int c1);
-void get_eval_class_threads(int *c0, int *c1);
+// The most boards that go without binning, in one launch with a workgroup each.
+int eval_few_boards(int cus, int slots);
+// Threads per root (256 or 512; a pair of roots takes twice as many) with 9 or 10
+// empty cells (cls 0), 8 (1) and 7 (2), set by the endgame autotuner;
+// process-wide.
+constexpr int kEvalThreadClasses = 3;
+void set_eval_class_threads(int cls, int threads);
+int get_eval_class_threads(int cls);
 hipError_t launch_eval_group(const uint64_t *boards, int e, int first, int count, uint4 *out,
                              const EvalScratch &S, const DevTables &T, hipStream_t s);
 

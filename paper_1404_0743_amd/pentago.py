@@ -109,6 +109,7 @@ _SIGS = {
     "pentago_debug_sym": ([_P, ctypes.c_int, _P, _P], ctypes.c_int),
     "pentago_debug_sym_pattern": ([ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, _P, _P],
                                   ctypes.c_int),
+    "pentago_debug_eval_threads": ([_P, _P], ctypes.c_int),
     "pentago_debug_layout": ([Section, ctypes.c_int, _P, _P], ctypes.c_int),
     "pentago_debug_swap3": ([_P, ctypes.c_int, _P], ctypes.c_int),
 }
@@ -390,8 +391,8 @@ def pentago_eval_batch(boards, out, status=None, stream=None, grouped=False):
 
 
 def pentago_autotune_eval(boards, out, stream=None):
-    """Time the endgame classes' workgroup sizes on these boards, keep the
-    fastest; returns ((threads of class 0, of class 1), best ms)."""
+    """Time the endgame's workgroup sizes on these boards, keep the faster;
+    returns ((threads per root with 8, with 7 empty cells), best ms)."""
     n = boards.numel() * boards.element_size() // 8
     th = (ctypes.c_int * 2)()
     ms = ctypes.c_float()
@@ -561,3 +562,12 @@ def pentago_debug_layout(counts, reps=False):
     _check(lib().pentago_debug_layout(section(counts), 1 if reps else 0, ctypes.byref(shape), ctypes.byref(sib)),
            "pentago_debug_layout")
     return {"lines": shape.lines, "threads": shape.threads, "order": shape.order}, bool(sib.value)
+
+
+def pentago_debug_eval_threads(threads=None):
+    """Threads per root with 9 or 10, with 8 and with 7 empty cells, before
+    they are set to threads, if given."""
+    new = None if threads is None else (ctypes.c_int * 3)(*threads)
+    old = (ctypes.c_int * 3)()
+    _check(lib().pentago_debug_eval_threads(new, old), "pentago_debug_eval_threads")
+    return tuple(old)

@@ -84,3 +84,40 @@ def test_roots_of_eight_do_not_wait_for_the_deepest(P, roots):
         ms[name] = best_ms(lambda: P.pentago_eval_batch_noalloc(dev, out))
     print(ms, flush=True)
     assert ms["both"] < ms["deepest"] + 0.5 * ms["eights"], ms
+
+
+@pytest.fixture
+def threads(P):
+    """Sets the threads per root; those from before come back at the end."""
+    kept = P.pentago_debug_eval_threads()
+    yield P.pentago_debug_eval_threads
+    P.pentago_debug_eval_threads(kept)
+
+
+@pytest.mark.parametrize("deep", (256, 512))
+@pytest.mark.parametrize("eight", (256, 512))
+def test_every_workgroup_size(P, roots, threads, deep, eight):
+    threads((deep, eight, 768 - eight))
+    boards, want = batch(roots, {10: 33, 9: 70, 8: 401, 5: 9}, deep + eight)
+    dev = codes(P, boards)
+    for call, fill in ((P.pentago_eval_batch, -1), (P.pentago_eval_batch_noalloc, -2)):
+        print(call.__name__, "threads", deep, eight, flush=True)
+        out = torch.full((len(boards), 8), fill, dtype=torch.int64, device="cuda")
+        call(dev, out)
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy().view(np.uint64), want)
+
+
+def test_autotuner_needs_roots_to_time(P, roots, threads):
+    """A few boards take a launch without these sizes, and roots of 5 empty
+    cells have none: tuning on them chooses nothing."""
+    for counts in ({8: 3, 5: 7}, {5: 3000}):
+        boards, _ = batch(roots, counts, 1)
+        dev = codes(P, boards)
+        out = torch.empty((len(boards), 8), dtype=torch.int64, device="cuda")
+        for size in ((256, 256, 512), (512, 256, 256), (256, 512, 512), (512, 512, 256)):
+            print("autotune", counts, size, flush=True)
+            threads(size)
+            got, ms = P.pentago_autotune_eval(dev, out)
+            assert ms > 0 and got == size[1:]
+            assert P.pentago_debug_eval_threads() == size
