@@ -668,7 +668,8 @@ static hipError_t launch_deep(int e, int mover, const unsigned cm0[4], const uns
         const void *kernel = !fits ? (const void *)deep_layer_kernel<1024, false>
                            : big   ? (const void *)deep_layer_kernel<1024, true>
                                    : (const void *)deep_layer_kernel<512, true>;
-        if (lds > 65536) err = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        // (the same bound from every thread: another's launch may lie between)
+        if (lds > 65536) err = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kDeepLds);
         if (err != hipSuccess) break;
         void *args[] = {&J};
         err = hipLaunchKernel(kernel, dim3(groups), dim3(nt), args, (size_t)lds, st);
