@@ -367,7 +367,6 @@ bool make_run(const pentago_section &s, SweepJob *J, int lds_cap)
         J->o1 = o[0];
         J->o2 = o[1];
         J->frun = R.start;
-        J->fruns = R.count;
         J->flines = R.max_patterns;
         J->fkids = R.max_children;
         J->ntiles = tiles;

@@ -298,7 +298,7 @@ struct alignas(16) DeepLocal {
 static_assert(sizeof(DeepLocal) == 64, "DeepLocal");
 
 struct DeepTables {
-    int e, mover;                 // empty cells; side to move at the root (1 black, 2 white)
+    int e;                        // empty cells
     uint2 own, other;             // the root's stones of the mover and the other side (as PairRoot)
     uint2 slot[kDeepMaxEmpty];
     // per subset mask of the cells: its colex rank; per size, the masks by rank
@@ -383,8 +383,8 @@ __global__ void __launch_bounds__(256) deep_tables_kernel(DeepTables D, DevTable
 }
 
 struct DeepLayer {
-    int e, t, mover;
-    int sx, sy;                   // stones of the side to move and of the other side in the cells
+    int e, t;
+    int sy;                       // stones in the cells of the side that does not move (sx: of the one that does)
     uint32_t parents, children;   // nodes of a block, of a child block
     uint32_t inner;               // layer t - 1 reads this layer in blocks of x masks: C(e - sx, sy) nodes each
     uint32_t blocks, per_group;   // blocks of the layer, blocks of a workgroup
@@ -610,14 +610,13 @@ size_t deep_scratch_bytes(int e, bool half)
 }
 
 // The whole-table solve: one launch for the tables, one per layer.
-static hipError_t launch_deep(int e, int mover, const unsigned cm0[4], const unsigned om0[4], const int *slot_q,
+static hipError_t launch_deep(int e, const unsigned cm0[4], const unsigned om0[4], const int *slot_q,
                               const int *slot_l, char *base, uint4 *out, const DevTables &T, hipStream_t st)
 {
     const DeepPlan P = deep_plan(e);
     DeepTables D;
     memset(&D, 0, sizeof(D));
     D.e = e;
-    D.mover = mover;
     D.own = make_uint2(cm0[0] | (cm0[1] << 9), cm0[2] | (cm0[3] << 9));
     D.other = make_uint2(om0[0] | (om0[1] << 9), om0[2] | (om0[3] << 9));
     for (int i = 0; i < e; i++) {
@@ -639,12 +638,11 @@ static hipError_t launch_deep(int e, int mover, const unsigned cm0[4], const uns
         memset(&J, 0, sizeof(J));
         J.e = e;
         J.t = t;
-        J.mover = mover;
-        J.sx = deep_movers(t);
-        J.sy = t - J.sx;
-        J.parents = (uint32_t)binom_host(e - J.sy, J.sx);
-        J.children = (uint32_t)binom_host(e - J.sy, J.sx + 1);
-        J.inner = (uint32_t)binom_host(e - J.sx, J.sy);
+        const int sx = deep_movers(t);
+        J.sy = t - sx;
+        J.parents = (uint32_t)binom_host(e - J.sy, sx);
+        J.children = (uint32_t)binom_host(e - J.sy, sx + 1);
+        J.inner = (uint32_t)binom_host(e - sx, J.sy);
         J.blocks = (uint32_t)binom_host(e, J.sy);
         // at least 16 waves' worth of nodes to a workgroup, as far as LDS goes
         const bool big = (size_t)J.children * 64 > 49152;
@@ -759,7 +757,7 @@ int eval_deep_enqueue(uint64_t packed, uint4 *out, hipStream_t st, int parity)
     err = hipMallocAsync((void **)&base, deep_scratch_bytes(e, half), st);
     if (err != hipSuccess) return hip_fail(err, "hipMallocAsync(deep scratch)");
     if (!half) {
-        err = launch_deep(e, J.mover, J.cm0, J.om0, J.slot_q, J.slot_l, base, out, T, st);
+        err = launch_deep(e, J.cm0, J.om0, J.slot_q, J.slot_l, base, out, T, st);
         (void)hipFreeAsync(base, st);
         if (err != hipSuccess) return hip_fail(err, "deep endgame launch");
         return 0;

@@ -90,8 +90,8 @@ __device__ __forceinline__ void five_entry(const DevTables &T, const unsigned xm
     tab[PL ? smax + r : 2 * r + 1] = make_uint4(F.w[4], F.w[5], F.w[6], F.w[7]);
 }
 
-// Solve one root with a group of GROUP threads: the whole workgroup (256 or
-// 512) or a wave or part of one (64, 32, 16).  `buf0` and `buf1` hold
+// Solve one root with a group of GROUP threads: the whole workgroup (256 and
+// more) or a wave (64).  `buf0` and `buf1` hold
 // two layers of A/B records, room for `cap` nodes each; `ftab` the five-set
 // tables (three with 512 threads or more, else two); slot_q/slot_l (10 ints
 // each, LDS) the root's empty cells.
@@ -119,9 +119,6 @@ __device__ void solve_root(const RootInfo &R, const DevTables &T, uint4 *buf0, u
 {
     constexpr bool WG = GROUP >= 256;
     constexpr bool WIDE = GROUP >= 512;
-    // GROUP < 64: a part of a wave; the other parts of the wave solve roots
-    // with as many empty cells, so that every wave barrier below is reached
-    // by all of them together
     const int lane = WG ? (int)threadIdx.x : (int)(threadIdx.x & (GROUP - 1));
     if (lane == 0) {
         int n = 0;
@@ -561,7 +558,12 @@ constexpr int kWaveLdsBytes = 2 * 90 * 64 + 2 * 20 * 32;
 
 // A batch whose roots all fall in one class (the server batches its searches
 // by empty cells): the roots are taken in order from one device queue, with
-// no binning pass.  Boards the class cannot hold get zero tables.
+// no binning pass.  Boards the class cannot hold get zero tables.  These are
+// the kernels of one root to a workgroup or wave (solve_root), also where
+// pentago_eval_batch solves pairs: the server's batches have not been moved to
+// solve_pairs, and a form with several small roots to a wave, correct in the
+// serving tests, once stopped making progress under load for a cause that was
+// not found.
 template <int CLS>
 __global__ void __launch_bounds__(256)
     eval_direct_kernel(const uint64_t *boards, int n, unsigned long long *counter, uint4 *out,
@@ -687,9 +689,8 @@ hipError_t launch_lookup(const uint64_t *boards, const int *sec_of, int n,
 }
 
 hipError_t launch_eval_bin(const uint64_t *boards, size_t n, const EvalScratch &S, int *status,
-                           uint4 *out, const DevTables &T, hipStream_t s)
+                           uint4 *out, hipStream_t s)
 {
-    (void)T;
     if (n <= (size_t)kBinSmall) {
         hipLaunchKernelGGL(eval_bin_small_kernel, dim3(1), dim3(1024), 0, s, boards, (int)n, S.start, S.order,
                            S.counter, status, out);
@@ -790,7 +791,7 @@ hipError_t launch_eval(const uint64_t *boards, size_t n, uint4 *out, const EvalS
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
     if (n <= (size_t)eval_few_boards(cus, S.global_slots)) return launch_few(boards, n, out, S, status, T, s);
-    e = launch_eval_bin(boards, n, S, status, out, T, s);
+    e = launch_eval_bin(boards, n, S, status, out, s);
     if (e != hipSuccess) return e;
     const bool cd = g_class_threads[0] == 512, c0 = g_class_threads[1] == 512, c1 = g_class_threads[2] == 512;
     e = cd ? launch_deepest<512>(n, cus, s, boards, S, out, T) : launch_deepest<256>(n, cus, s, boards, S, out, T);

@@ -42,7 +42,9 @@ int eval_grid(int *grid)
     int cus = 0;
     e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
-    // two 256-thread workgroups per CU fit the LDS of the deepest in-LDS DAG
+    // workgroups with a layer slot of their own for roots with 9 or 10 empty
+    // cells, and those of the server's batches with 8 to 10: two per CU, as the
+    // LDS of one root with 8 allows
     *grid = std::max(1, 2 * cus);
     if (dev < 64) cached[dev] = *grid;
     keep_pool(dev);
@@ -204,7 +206,7 @@ int pentago_eval_batch_grouped(const pentago_board *boards, size_t n, pentago_su
     EvalAlloc A;
     rc = eval_alloc(n, grid, st, &A);
     if (rc) return rc;
-    hipError_t e = launch_eval_bin((const uint64_t *)boards, n, A.S, status, (uint4 *)out, T, st);
+    hipError_t e = launch_eval_bin((const uint64_t *)boards, n, A.S, status, (uint4 *)out, st);
     int start[16];
     if (e == hipSuccess) e = hipMemcpyAsync(start, A.S.start, sizeof(start), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);

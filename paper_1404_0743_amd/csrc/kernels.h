@@ -80,8 +80,8 @@ struct SweepJob {
     int order;         // tile order of the one-section sweep (0 natural, 1 by XCD)
     // Tiles of sibling lines (sweep_run_tile): the second staged quadrant, whose
     // patterns have one empty cell (-1: none), the first of its class's runs in
-    // run_start, their number, and the most lines and child lines of one.
-    int fam, frun, fruns, flines, fkids;
+    // run_start, and the most lines and child lines of one.
+    int fam, frun, flines, fkids;
     // Children held as their representatives under the board symmetries:
     // child[j] is then the table of a section whose image under symmetry
     // csym[j] is child j (0: child[j] is child j itself); rm[j] is that
@@ -124,7 +124,7 @@ struct EvalScratch {
 };
 
 hipError_t launch_eval_bin(const uint64_t *boards, size_t n, const EvalScratch &S, int *status,
-                           uint4 *out, const DevTables &T, hipStream_t s);
+                           uint4 *out, hipStream_t s);
 // Solve n boards: a batch no larger than the workgroups that run at once in
 // one launch, else binned by empty cells and solved by one persistent launch
 // per class (S.global_slots layer slots for roots with 9 or 10 empty cells).

@@ -826,9 +826,8 @@ __device__ __forceinline__ void sweep_run_tile(const SweepJob &J, const DevTable
         }
     }
     const int sst = sel_stride(mD);
-    if (wave > 0 || nwaves == 1) {
-        const int skip = nwaves == 1 ? 0 : 64;
-        for (int it = tid - skip; it < mD + cmD; it += (int)blockDim.x - skip) {
+    if (wave > 0) {
+        for (int it = tid - 64; it < mD + cmD; it += (int)blockDim.x - 64) {
             const int p = it < mD ? J.qb[D] + it : J.cqb[D] + (it - mD);
             const uint4 *ps = T.pat_sel + 2 * (((D * kPatterns + p) << 1) + c - 1);
             const uint4 sc = ps[0], so = ps[1];
@@ -1064,8 +1063,7 @@ __device__ __forceinline__ void sweep_run_any(const SweepJob &J, const DevTables
     }
 }
 
-template <int NT>
-__global__ void __launch_bounds__(NT, 6) sweep_run_kernel(SweepJob J, DevTables T)
+__global__ void __launch_bounds__(512, 6) sweep_run_kernel(SweepJob J, DevTables T)
 {
     // the job where it lies, in the kernel arguments: a job passed by value and
     // indexed by quadrant would be copied to scratch
@@ -1096,8 +1094,8 @@ hipError_t launch_sweep(const SweepJob &job, const DevTables &T, hipStream_t s)
     const dim3 grid((unsigned)job.ntiles), block(job.threads);
     if (job.threads != 256 && job.threads != 512) return hipErrorInvalidValue;
     if (job.fam >= 0) {
-        if (job.threads == 512) hipLaunchKernelGGL(sweep_run_kernel<512>, grid, block, job.lds_bytes, s, job, T);
-        else hipLaunchKernelGGL(sweep_run_kernel<256>, grid, block, job.lds_bytes, s, job, T);
+        if (job.threads != 512) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(sweep_run_kernel, grid, block, job.lds_bytes, s, job, T);
         return hipGetLastError();
     }
     const bool symc = job.csym[job.d & 3] != 0 && ((job.emask >> job.d) & 1) && !((job.odmask >> job.d) & 1);
