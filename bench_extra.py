@@ -110,7 +110,7 @@ def endgame(P, torch, stream, boards, grouped_too):
         # VALU issue of the persistent form: the class kernels' instructions
         # (committed counters, while their sources are unchanged) over its time
         import bench
-        per = [bench.profile_counts("eval_persistent_kernel_class%d_2p20_roots_valu" % c) for c in range(3)]
+        per = [bench.profile_counts("eval_pairs_kernel_class%d_2p20_roots_valu" % c) for c in range(3)]
         if all(p is not None for p in per):
             instr = sum(p["valu_instr"] for p in per)
             res["roofline_valu"] = {"bound": "alu", "achieved": instr / (med * 1e-3) / 1e9,
@@ -478,9 +478,10 @@ def slices(P, torch, stream):
 def deep(P, torch, stream):
     """One position of 22, 20 and 18 stones (14, 16, 18 empty cells) from
     random legal play, each solved from scratch by pentago_eval_deep.
-    Algorithmic bytes: 64 B read per (node, child) edge + 64 B written per
-    node below the root; half of that for the parity-halved form (32 B
-    records, the rotations of the board's own parity only)."""
+    Bytes: every node's 64 B record written once and read once.  The
+    parity-halved form (32 B records, the rotations of the board's own parity
+    only) reads a record per (node, child) edge, from L2 where neighbours share
+    it; its algorithmic bytes count every edge."""
     out = torch.zeros(8, dtype=torch.int64, device="cuda")
     res = {}
     for stones in (22, 20, 18):
@@ -488,7 +489,7 @@ def deep(P, torch, stream):
         codes = P.boards_to_codes(b.reshape(1, 36))[0]
         e = 36 - stones
         nodes = [math.comb(e, t) * math.comb(t, (t + 1) // 2) for t in range(e + 1)]
-        alg = 64 * sum(n * (e - t) for t, n in enumerate(nodes)) + 64 * sum(nodes[1:])
+        half_alg = 32 * sum(n * (e - t) for t, n in enumerate(nodes)) + 32 * sum(nodes[1:])
         med, mn = _time(torch, stream, lambda: P.pentago_eval_deep(codes, out, stream), 5)
         # the same root through the batched solver's layout limit: not
         # comparable beyond 10 empty cells, so the check is the recurrence and
@@ -497,7 +498,7 @@ def deep(P, torch, stream):
         P.pentago_eval_deep(codes, out, stream)
         torch.cuda.synchronize()
         # the parity-halved form (32 B records) for the board's own parity
-        # (g = 0): half the algorithmic bytes; its bits equal the full table's
+        # (g = 0): its bits equal the full table's
         half = torch.zeros(8, dtype=torch.int64, device="cuda")
         hmed, hmn = _time(torch, stream, lambda: P.pentago_eval_deep_parity(codes, 0, half, stream), 5)
         torch.cuda.synchronize()
@@ -505,22 +506,17 @@ def deep(P, torch, stream):
         fw = out.cpu().numpy().view(np.uint64)
         # floor bytes: every node's record written once and read once
         floor = 2 * 64 * sum(nodes)
-        prof = bench_profile("deep_node_kernel_valu")
+        prof = bench_profile("deep_layer_kernel_valu")
         res["empty%d" % e] = {"stones": stones, "dag_nodes": sum(nodes), "ms": med, "min_ms": mn,
                               "valu_issue_frac_profiled": None if prof is None else
-                              {"full": prof["deep_node_kernel<false>"]["valu_issue_frac"],
-                               "parity_half": prof["deep_node_kernel<true>"]["valu_issue_frac"]},
+                              {"full": prof["deep_layer_kernel"]["valu_issue_frac"],
+                               "parity_half": prof["deep_half_kernel"]["valu_issue_frac"]},
                               "nodes_per_s": sum(nodes) / (med * 1e-3),
-                              # 64 B per (node, child) edge read + 64 B per node
-                              # written: L2 serves part of the edge reads, so
-                              # this is not an HBM fraction
-                              "algorithmic_GB_s": alg / (med * 1e-3) / 1e9,
-                              "algorithmic_frac": alg / (med * 1e-3) / 8e12,
                               "floor_GB_s": floor / (med * 1e-3) / 1e9,
                               "floor_frac_hbm": floor / (med * 1e-3) / 8e12,
                               "repeatable": bool(torch.equal(first, out)),
                               "parity_half_ms": hmed, "parity_half_min_ms": hmn,
-                              "parity_half_algorithmic_GB_s": alg / 2 / (hmed * 1e-3) / 1e9,
+                              "parity_half_algorithmic_GB_s": half_alg / (hmed * 1e-3) / 1e9,
                               "parity_half_floor_frac_hbm": floor / 2 / (hmed * 1e-3) / 8e12,
                               "parity_half_equals_full_masked": bool(np.array_equal(hw, fw & PARITY0)),
                               "parity_half_bits": int(sum(bin(int(x)).count("1") for x in hw))}
