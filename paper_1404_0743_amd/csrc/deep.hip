@@ -383,18 +383,18 @@ __global__ void __launch_bounds__(256) deep_tables_kernel(DeepTables D, DevTable
 }
 
 struct DeepLayer {
-    int e, t;
-    int sy;                       // stones in the cells of the side that does not move (sx: of the one that does)
-    uint32_t parents, children;   // nodes of a block, of a child block
-    uint32_t inner;               // layer t - 1 reads this layer in blocks of x masks: C(e - sx, sy) nodes each
-    uint32_t blocks, per_group;   // blocks of the layer, blocks of a workgroup
-    uint32_t parts;               // workgroups a block is split over (1 if its children are staged)
     const uint32_t *rank, *ylist;
     const uint4 *fx, *fy;         // five-sets of the two sides (by mask)
     const DeepLocal *local;
     const uint4 *prev;
     uint4 *cur;
     uint4 *out;
+    int e, t;
+    int sy;                       // stones in the cells of the side that does not move (sx: of the one that does)
+    uint32_t parents, children;   // nodes of a block, of a child block
+    uint32_t inner;               // layer t - 1 reads this layer in blocks of x masks: C(e - sx, sy) nodes each
+    uint32_t blocks, per_group;   // blocks of the layer, blocks of a workgroup
+    uint32_t parts;               // workgroups a block is split over (1 if its children are staged)
 };
 
 // ~fo & rmin(u) of a quad's node (layout above): dimension 0 flips p0, which
