@@ -150,6 +150,10 @@ def random_play_boards(n, stones_lo, stones_hi, seed=SEED_BATCH, workers=None):
     else:
         with mp.get_context("fork").Pool(procs) as pool:
             parts = pool.map(_play_chunk, args)
+            # the workers end by themselves: a profiler's signal handler, which
+            # they inherit, can hang in one that is terminated
+            pool.close()
+            pool.join()
     return np.concatenate(parts)
 
 
