@@ -424,14 +424,15 @@ __device__ __forceinline__ void unpack4(uint32_t (&w)[4], const uint4 v)
 // One layer.  A workgroup takes per_group blocks: it copies their children,
 // which lie one after another, into LDS, and its waves take 16 nodes of one
 // block at a time from there.  18 empty cells: 5.47 -> 3.65 ms a solve with the
-// node-per-thread form before; 12.2 GB of HBM traffic in place of 28 (11.1 GB
-// are the records written and read once), VALU issue at 0.4 of the peak and
-// 170 instructions a lane, the rest the chain of table loads in front of every
-// 16 nodes.  (Read from L2 by each parent instead, the blocks
+// node-per-thread form before; 12.5 GB of HBM traffic in place of 28 (11.1 GB
+// are the records written and read once), VALU issue at 0.47 of the peak with
+// 196 instructions of a wave to 16 nodes, the rest the chain of table loads in
+// front of them.  (Read from L2 by each parent instead, the blocks
 // in flight on an XCD, 50 KB and more each, exceed its L2: 15.4 GB came from
 // HBM for 18 empty cells, against 5.5 GB of records.)  Blocks of more than 2500
 // children (19 and 20 empty cells) do not fit: STAGED = false reads them from
-// memory, several workgroups to a block.
+// memory, several workgroups to a block (19 empty cells 16.1 -> 11.6 ms, 20
+// 48.6 -> 38.3 ms with the form before).
 template <int NT, bool STAGED>
 __global__ void __launch_bounds__(NT, 8) deep_layer_kernel(DeepLayer J)
 {

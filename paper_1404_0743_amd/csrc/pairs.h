@@ -24,9 +24,10 @@
 // next layer): 7 instructions for 32 bits, against 17 in the layout of
 // Set256, where the p_j of dimensions 0 and 1 are bits of the same word.
 //
-// What bounds it: VALU issue and LDS reads alike (8 empty cells: 0.6 of the
-// issue peak, LDS busy for half of the time with one 1024-thread workgroup per
-// CU); the layers' barriers leave the rest.  ns per root, 131,072 roots of one
+// What bounds it: VALU issue and LDS reads alike (8 empty cells, one 1024-thread
+// workgroup per CU: 0.60 of the issue peak; an LDS instruction in 19 cycles, of
+// the 8 that 16 bytes a lane take, and bank conflicts in 0.15 of the cycles);
+// the layers' barriers leave the rest.  ns per root, 131,072 roots of one
 // size, against one root per workgroup or wave in the layout of Set256:
 //   empty cells    3      4      5      6      7      8
 //   one root      2.42   3.92   6.99  13.84  28.79  77.76
