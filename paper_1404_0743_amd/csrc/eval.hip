@@ -150,6 +150,23 @@ int pentago_autotune_eval(const pentago_board *boards, size_t n, pentago_superin
     if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
     int rc = eval_grid(&grid);
     if (rc) return rc;
+    // the classes these boards have roots of: a batch that goes without binning
+    // reaches none of their kernels
+    int roots[kEvalThreadClasses] = {0, 0, 0};
+    if (n > (size_t)eval_few_boards(cus, (int)std::min<size_t>(n, (size_t)grid))) {
+        EvalAlloc A;
+        rc = eval_alloc(n, grid, st, &A);
+        if (rc) return rc;
+        int start[16];
+        e = launch_eval_bin((const uint64_t *)boards, n, A.S, nullptr, (uint4 *)out, st);
+        if (e == hipSuccess) e = hipMemcpyAsync(start, A.S.start, sizeof(start), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        (void)hipFreeAsync(A.base, st);
+        if (e != hipSuccess) return hip_fail(e, "eval launch");
+        roots[0] = start[8];
+        roots[1] = start[7] - start[8];
+        roots[2] = start[6] - start[7];
+    }
     hipEvent_t a, b;
     if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess)
         return fail(PENTAGO_EDEVICE, "hipEventCreate");
@@ -168,11 +185,10 @@ int pentago_autotune_eval(const pentago_board *boards, size_t n, pentago_superin
         return t;
     };
     float best = time();
-    // The classes' launches follow one another, so each size is tried by itself.
-    // A batch that goes without binning has none of them, and one without roots
-    // of a class times only noise: a size changes where it gains 2 %.
-    const bool binned = n > (size_t)eval_few_boards(cus, (int)std::min<size_t>(n, (size_t)grid));
-    for (int cls = 0; cls < kEvalThreadClasses && binned && rc == 0; cls++) {
+    // The classes' launches follow one another, so each size is tried by itself;
+    // it changes where that gains 2 %, more than repeated runs differ.
+    for (int cls = 0; cls < kEvalThreadClasses && rc == 0; cls++) {
+        if (roots[cls] == 0) continue;
         const int kept = get_eval_class_threads(cls);
         set_eval_class_threads(cls, 768 - kept);
         const float t = time();
